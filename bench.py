@@ -82,37 +82,26 @@ def _load_traffic(kernel: str, workload: str, variant: str = None):
 # Kernel symbols, and the summaries of rocprofv3 output committed under profiles/
 # ---------------------------------------------------------------------------
 
-def _rows_of(seg_bytes: int, row_bytes: int) -> int:
-    """Rows of `row_bytes` per segment when that is 1, 2, 4, 8 or 16 (the copy kernels' fast paths)."""
-    if seg_bytes % row_bytes:
-        return 0
-    r = seg_bytes // row_bytes
-    return r if r in (1, 2, 4, 8, 16) else 0
-
-
 def _symbol(kind: str, w) -> str:
-    """The __global__ function (copy.hip) a copy launch of this kind runs for the workload's segment size."""
+    """The __global__ function (copy.hip) a large copy launch of this kind runs for the workload's segment size
+    (store and stream: more than 1 GiB of payload; unit and pair: more than 640 MiB, or segments of 32 KiB and
+    up).  Smaller launches run small_copy_kernel, segments outside 512 bytes .. 512 KiB copy_generic_kernel."""
     seg = w.shape.seg_bytes
+    if kind == "quad" and seg in (4096, 8192, 16384, 32768, 65536):
+        return f"retrieve_quad_kernel<{seg // 4096}>"
+    retrieve = kind != "store"
+    if not 512 <= seg <= 512 << 10:
+        return f"copy_generic_kernel<{'true' if retrieve else 'false'}>"
     if kind in ("unit", "pair", "quad"):
-        r = _rows_of(seg, 256 * 16)
-        if kind == "pair" and r != 8:
-            kind = "unit"
-        if r:
-            return {"unit": "retrieve_unit_kernel", "pair": "retrieve_pair_kernel",
-                    "quad": "retrieve_quad_kernel"}[kind] + f"<{r}>"
-        return "copy_generic_kernel<true>"
-    retrieve = kind == "stream"
-    for t in (1024, 512, 256):
-        r = _rows_of(seg, t * 16)
-        if r:
-            return f"group_copy_kernel<{t}, {r}, {'true' if retrieve else 'false'}>"
-    return f"copy_generic_kernel<{'true' if retrieve else 'false'}>"
+        return f"retrieve_unit_kernel<{1 if seg % 1024 == 0 else 0}>"
+    row = 2 if seg % 16384 == 0 else 1 if seg % 1024 == 0 else 0
+    return f"group_copy_kernel<{256 if retrieve and seg < 16384 else 1024}, {row}, {'true' if retrieve else 'false'}>"
 
 
 def _label(symbol: str) -> str:
     """What a library kernel does, from its symbol."""
-    for key, text in (("retrieve_unit_kernel", "retrieve scatter, unit walk (KV_RETRIEVE_UNIT)"),
-                      ("retrieve_pair_kernel", "retrieve scatter, pair walk (KV_RETRIEVE_PAIR)"),
+    for key, text in (("retrieve_unit_kernel", "retrieve scatter, shared chunks (KV_RETRIEVE_UNIT, KV_RETRIEVE_PAIR)"),
+                      ("small_copy_kernel", "retrieve scatter or store gather, small launch"),
                       ("retrieve_quad_kernel", "retrieve scatter, four-job window (KV_RETRIEVE_QUAD)"),
                       ("copy_generic_kernel<true>", "retrieve scatter, generic path"),
                       ("copy_generic_kernel<false>", "store gather, generic path"),

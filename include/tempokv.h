@@ -241,28 +241,23 @@ int kv_retrieve_scatter(const kv_layout *layout, const void *d_staging, void *co
 /* Variants of the retrieve.  All give the bytes of kv_retrieve_scatter for
  * any job list; they differ in speed by the way jobs share staged chunks. */
 typedef enum kv_retrieve_kind {
-    KV_RETRIEVE_UNIT = 0,   /* one workgroup per (job, layer, plane) unit; jobs that share a chunk read it
+    KV_RETRIEVE_UNIT = 0,   /* groups of 512 KiB or more, job after job: jobs that share a chunk read a group
                                through the L2 (kv_retrieve_scatter) */
-    KV_RETRIEVE_PAIR = 1,   /* one workgroup per pair of consecutive jobs: a pair naming one chunk reads each
-                               stage once and writes it twice (32 KiB segments; other sizes use UNIT) */
-    KV_RETRIEVE_STREAM = 2, /* 1024-lane workgroups, non-temporal loads of the staged chunks: for lists that
-                               read each chunk once */
+    KV_RETRIEVE_PAIR = 1,   /* runs as UNIT, which is the faster also where pairs of jobs name one chunk */
+    KV_RETRIEVE_STREAM = 2, /* non-temporal loads of the staged chunks: for lists that read each chunk once */
     KV_RETRIEVE_QUAD = 3    /* one 1024-lane workgroup per (layer, plane, 4 consecutive jobs, segment): jobs of
                                the window that share a chunk load it together, one read from memory and the
-                               rest from L2.  Segments of 4, 8, 16, 32 or 64 KiB (other sizes use the generic
-                               copy).  Never returned by kv_retrieve_plan: whether it beats PAIR/UNIT depends on
-                               where the paged pool lies in physical memory (it does on most placements
-                               measured, by about 6 %, and loses where scattered writes run fast), so a caller
-                               picks it by timing both on its own pool. */
+                               rest from L2.  Segments of 4, 8, 16, 32 or 64 KiB (other sizes run as UNIT).
+                               Never returned by kv_retrieve_plan: whether it beats UNIT depends on where the
+                               paged pool lies in physical memory, so a caller picks it by timing both on its
+                               own pool. */
 } kv_retrieve_kind;
 
 /* Pick the variant for a job list from its host copy (grouped by slot, as
  * kv_group_jobs_by_slot leaves it): STREAM when every slot appears once; PAIR
  * when the segments are 32 KiB, at least 90 % of the job pairs (0,1), (2,3),
  * ... name one slot and the groups of equal slots average at most 16 jobs;
- * UNIT otherwise.  The thresholds are measured (lists with groups of 8, as in
- * a batch whose requests share a handful of prefixes, gain 3-13 % from PAIR;
- * irregular or very large groups lose 1-3 %).  Returns a kv_retrieve_kind, or
+ * UNIT otherwise.  PAIR and UNIT run the same copy.  Returns a kv_retrieve_kind, or
  * KV_EINVAL / a layout error. */
 int kv_retrieve_plan(const kv_layout *layout, const kv_job *h_jobs, int32_t num_jobs);
 

@@ -94,8 +94,8 @@ int kv_retrieve_scatter_as(int32_t kind, const kv_layout *layout, const void *d_
                            int32_t num_jobs, void *stream) {
     tkv::CopyKind k;
     switch (kind) {
-    case KV_RETRIEVE_UNIT: k = tkv::kRetrieve; break;
-    case KV_RETRIEVE_PAIR: k = tkv::kRetrievePair; break;
+    case KV_RETRIEVE_UNIT:
+    case KV_RETRIEVE_PAIR: k = tkv::kRetrieve; break;
     case KV_RETRIEVE_STREAM: k = tkv::kRetrieveStream; break;
     case KV_RETRIEVE_QUAD: k = tkv::kRetrieveQuad; break;
     default: return KV_EINVAL;

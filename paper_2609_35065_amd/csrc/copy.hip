@@ -8,42 +8,34 @@
 // A row is one 16-byte vector per lane of a workgroup (T*16 bytes, one wave
 // instruction per 64 lanes covering 1 KiB of contiguous memory).
 //
-// Retrieve (staging -> paged), fast path: one 256-lane workgroup per unit.
-// The unit's staged bytes are read front to back in stages of 8 vectors per
-// lane; the loads of stage s+1 are issued before the stores of stage s, and
-// the workgroup waits for both before going on, so it keeps one segment of
-// writes in flight (more was measured slower where chunks are shared).
-// Block ids come through the scalar cache.
-// Units are ordered (layer, plane)-major and job-minor, and each of the 8
-// XCDs walks one contiguous range of that order, so the jobs that share a
-// staged chunk (requests reusing one prefix; adjacent once the job list is
-// grouped by slot) read the same 512 KiB back to back through one XCD's L2.
-// Loads are cached; paged writes are non-temporal.
+// A window is V consecutive 1 KiB rows of a staged slot (one 16-byte vector
+// per lane of one wave and row).  The staged side of a window is contiguous;
+// on the paged side it covers parts of one or more segments, of one or two
+// planes, whatever the segment size.
 //
-// Store (paged -> staging), fast path: 1024-lane workgroups, each copying a
-// group of segments with 16 vectors per lane in flight (256 KiB per
-// workgroup for 32 KiB segments), all loads before all stores; job-major
-// order, each XCD taking one contiguous range of it, so a die fills whole
-// staging slots front to back.  Both loads and stores are non-temporal: each
-// byte is touched once.  The same kernel in the other direction is the
-// streaming retrieve, for job lists in which no staged chunk is read twice:
-// there is no reuse to keep in cache, and it is 3-6 % faster than the unit
-// walk on such lists (much slower where chunks are shared).
+// Both directions run copy_window: one wave per window, T/64 consecutive
+// windows per workgroup, all loads of a window before its stores.  What bounds
+// a copy is how the memory system takes its order of reads and writes, so the
+// three shapes differ in how much a wave moves and which windows are in flight
+// together:
 //
-// The pair retrieve walks two consecutive jobs per workgroup and, when they
-// name one staged chunk, loads each stage once for both: with groups of 8
-// requests per chunk it is 3-13 % faster than the unit walk.  The host picks
-// among these three retrieves from the job list (kv_retrieve_plan).  A fourth,
-// the four-job-window retrieve (one segment of four consecutive jobs per
-// 1024-lane workgroup), is faster than the pair walk on pools where the memory
-// system takes scattered writes slowly and slower elsewhere, so the caller
-// picks it by timing.
+//   Store and streaming retrieve (no staged byte read twice): job-major order,
+//   each XCD taking one contiguous range of it, non-temporal on both sides.
+//   Large launches move 16 KiB per wave in 1024-lane workgroups; small ones
+//   2 KiB per wave, so that every CU has work and the first store is issued
+//   early (stream_shape below has the sizes and times).
 //
-// On MI355X these shapes were chosen by measurement: at 256 lanes a plain
-// contiguous copy tops out near 5.2 TB/s (read + write), at 1024 lanes near
-// 5.9 TB/s; the 256-lane walks are the fastest retrieves where chunks are
-// shared because their stores are scattered 32 KiB blocks while their loads
-// hit in cache.
+//   Retrieve where jobs share staged chunks: 4 KiB per wave, 256-lane
+//   workgroups, in groups of windows (512 KiB or more); a group of one job is
+//   followed by the same group of the next job, and each XCD takes one
+//   contiguous range of that order.  Jobs that share a chunk (adjacent once
+//   the job list is grouped by slot) read the group through one XCD's L2 while
+//   it is there, and a paged block is written by workgroups that run together.
+//   Loads are cached, paged writes non-temporal.
+//
+// A further retrieve, the four-job-window retrieve (one segment of four
+// consecutive jobs per 1024-lane workgroup), is faster on some pools and
+// slower on others, so the caller picks it by timing.
 //
 // Generic path: any segment size that is a multiple of 16 bytes, one
 // 256-lane workgroup per segment.
@@ -80,157 +72,146 @@ __device__ __forceinline__ bool blk_ok(const CopyParams &p, int32_t blk) {
 constexpr int kXcds = 8;
 
 // --------------------------------------------------------------------------
-// Retrieve fast path: R rows of 4 KiB per segment (segment = R * 4 KiB).
+// Window copy.  Bound by the memory system: ~5.8-6.0 TB/s (read + write) for a
+// large store of 32 KiB segments and 5.3-5.6 TB/s for a retrieve, which is what
+// dense copies in the same shapes reach.
+//
+// Lane i of a wave looks up the paged address of the i-th segment that the
+// window touches; rows then take their segment's address from that lane
+// (kRow): 2, the first lane's for the whole window, where it lies in one
+// segment; 1, by v_readlane, where a row never crosses a segment (segments of
+// whole KiB); 0, lane by lane through ds_bpermute.  So any segment of at least
+// kMinWindowSeg bytes fills its lanes, where one workgroup per segment leaves
+// three of four waves of a 1 KiB segment without work: 512 jobs of 1 KiB
+// segments store in 0.19 ms (0.75 ms before), retrieve with shared chunks
+// (1,422 jobs) in 0.37 ms (2.07 ms before).
+//
+// The division of a row's vector index by the segment size is a multiply by
+// magic = ceil(2^32 / segv), exact while index * (magic * segv - 2^32) < 2^32:
+// the index is below segv + 1024 and the bracket below segv, so it holds for
+// segv <= 32768 (kMaxWindowSeg).
 // --------------------------------------------------------------------------
-template <int R>
-__global__ __launch_bounds__(256) void retrieve_unit_kernel(CopyParams p) {
-    constexpr int T = 256;
-    constexpr int SB = R >= 8 ? 1 : 8 / R;   // segments per pipeline stage
-    constexpr int V = R * SB;                // vectors per lane per stage
-    const int tid = threadIdx.x;
-    const int64_t units = (int64_t)p.num_jobs * p.L * 2;
-    const int64_t per_xcd = (units + kXcds - 1) / kXcds;
-    const int32_t nstage = (p.nseg + SB - 1) / SB;
-    // XCD-aware order: workgroup b runs on XCD b mod 8, so XCD x walks the
-    // contiguous range [x*per_xcd, (x+1)*per_xcd) of the unit order; the
-    // grid (and its stride) is a multiple of kXcds.
-    for (int64_t w = blockIdx.x; w < per_xcd * kXcds; w += gridDim.x) {
-        const int64_t u = (w % kXcds) * per_xcd + w / kXcds;
-        if (u >= units) continue;
-        const int64_t q = u % p.num_jobs;
-        const int64_t t = u / p.num_jobs;
-        const int32_t kv = (int32_t)(t & 1);
-        const int32_t l = (int32_t)(t >> 1);
+constexpr int64_t kMinWindowSeg = 512;        // V * 64 vectors touch at most 33 segments: one lane each
+constexpr int64_t kMaxWindowSeg = 512 << 10;
+
+struct WindowParams {
+    uint32_t segv;     // 16-byte vectors of a segment
+    uint32_t slotv;    // ... of a slot
+    uint32_t nsegs;    // segments of a slot
+    uint32_t magic;    // ceil(2^32 / segv)
+    uint32_t nwg;      // workgroups of a slot, a multiple of group
+    uint32_t group;    // consecutive workgroups of one job (shared retrieve)
+};
+
+enum WindowMode { kWinStore, kWinStream, kWinShared };
+
+template <int T, int V, WindowMode kMode, int kRow>
+__device__ __forceinline__ void copy_window(const CopyParams &p, const WindowParams &w) {
+    static_assert(V * 64 <= 1024, "the bound of magic and the lane table allow 1024 vectors a window");
+    constexpr uint32_t W = T / 64;
+    const uint32_t lane = threadIdx.x & 63;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t total = (uint32_t)p.num_jobs * w.nwg;   // below 2^31 (window_params)
+    const uint32_t per_xcd = (total + kXcds - 1) / kXcds;
+    // workgroup b runs on XCD b mod 8, so XCD x copies the contiguous range
+    // [x*per_xcd, (x+1)*per_xcd) of the order; the grid is a multiple of kXcds
+    for (uint32_t b = blockIdx.x; b < per_xcd * kXcds; b += gridDim.x) {
+        const uint32_t g = (b % kXcds) * per_xcd + b / kXcds;
+        if (g >= total) continue;
+        uint32_t q, wi;
+        if constexpr (kMode == kWinShared) {
+            const uint32_t h = g / w.group;
+            const uint32_t sw = h / (uint32_t)p.num_jobs;
+            q = h - sw * (uint32_t)p.num_jobs;
+            wi = sw * w.group + (g - h * w.group);
+        } else {
+            q = g / w.nwg;
+            wi = g - q * w.nwg;
+        }
+        const uint32_t v0 = (wi * W + wave) * (V * 64);   // first vector of the window in its slot
+        if (v0 >= w.slotv) continue;
         const v4i jb = ((const_job_ptr)p.jobs)[q];
         if (!job_ok(p, jb)) continue;
-        const const_i32_ptr btp = (const_i32_ptr)p.bt + (int64_t)jb.y * p.bt_stride + (int64_t)jb.z * p.nseg;
-        const v4u *src = reinterpret_cast<const v4u *>(p.staging + (int64_t)jb.x * p.slot_bytes +
-                                                       ((int64_t)l * 2 + kv) * p.nseg * p.seg_bytes) + tid;
-        char *dst_plane = p.layers[l] + kv * p.kv_stride;
 
-        v4u a[V], b[V];
-#pragma unroll
-        for (int k = 0; k < V; ++k)
-            if (k / R < p.nseg) a[k] = src[(int64_t)k * T];
-        for (int32_t s = 0; s < nstage; ++s) {
-            const int32_t s0 = s * SB;
-            if (s + 1 < nstage) {
-                const v4u *nsrc = src + (int64_t)(s0 + SB) * R * T;
-#pragma unroll
-                for (int k = 0; k < V; ++k)
-                    if (s0 + SB + k / R < p.nseg) b[k] = nsrc[(int64_t)k * T];
+        const uint32_t s0 = v0 / w.segv;
+        const uint32_t rel0 = v0 - s0 * w.segv;
+        uint32_t base_lo = 0, base_hi = 0;   // lane i: paged address of segment s0 + i, 0 where nothing is copied
+        const uint32_t s = s0 + lane;
+        if (s < w.nsegs && s * w.segv < v0 + V * 64) {
+            const uint32_t pl = s / (uint32_t)p.nseg;   // layer * 2 + plane
+            const int32_t blk = p.bt[(int64_t)jb.y * p.bt_stride + (int64_t)jb.z * p.nseg + (s - pl * p.nseg)];
+            if (blk_ok(p, blk)) {
+                const uint64_t a = (uint64_t)(p.layers[pl >> 1] + (int64_t)(pl & 1) * p.kv_stride +
+                                              (int64_t)blk * p.block_stride);
+                base_lo = (uint32_t)a;
+                base_hi = (uint32_t)(a >> 32);
             }
-#pragma unroll
-            for (int j = 0; j < SB; ++j) {
-                const int32_t seg = s0 + j;
-                if (seg >= p.nseg) break;
-                const int32_t blk = btp[seg];
-                if (!blk_ok(p, blk)) continue;
-                v4u *dst = reinterpret_cast<v4u *>(dst_plane + (int64_t)blk * p.block_stride) + tid;
-#pragma unroll
-                for (int r = 0; r < R; ++r) __builtin_nontemporal_store(a[j * R + r], dst + r * T);
-            }
-#pragma unroll
-            for (int k = 0; k < V; ++k) a[k] = b[k];
         }
-    }
-}
-
-// --------------------------------------------------------------------------
-// Retrieve, pairs of jobs (32 KiB segments): a unit is (jobs 2w and 2w+1,
-// layer, plane).  When both jobs name the same staged chunk, each stage of it
-// is loaded once and stored to both jobs' blocks; otherwise each job is walked
-// on its own.  Stages are ping-ponged between two register sets, and the
-// loads of the last stage are clamped to the unit so that every stage issues
-// the same instructions.
-// --------------------------------------------------------------------------
-template <int R, bool kTwo>
-__device__ __forceinline__ void pair_walk(const CopyParams &p, const char *src, const_i32_ptr rows0,
-                                          const_i32_ptr rows1, char *dst_plane, int tid) {
-    constexpr int T = 256;
-    constexpr int V = R;
-    const int32_t ns = p.nseg;
-    const int64_t seg = p.seg_bytes;
-    const v4u *base = reinterpret_cast<const v4u *>(src) + tid;
-    v4u A[V], B[V];
-#pragma unroll
-    for (int x = 0; x < V; ++x) A[x] = base[x * T];
-    for (int32_t s = 0; s < ns; s += 2) {
-        const int32_t s1 = s + 1 < ns ? s + 1 : ns - 1;
-        const v4u *n1 = reinterpret_cast<const v4u *>(src + (int64_t)s1 * seg) + tid;
-#pragma unroll
-        for (int x = 0; x < V; ++x) B[x] = n1[x * T];
-        {
-            const int32_t b0 = rows0[s];
-            if (blk_ok(p, b0)) {
-                v4u *d = reinterpret_cast<v4u *>(dst_plane + (int64_t)b0 * p.block_stride) + tid;
-#pragma unroll
-                for (int x = 0; x < V; ++x) __builtin_nontemporal_store(A[x], d + x * T);
+        // paged address of this lane's vector in row k, or null
+        auto paged = [&](int k) -> v4u * {
+            uint32_t lo, hi, off;
+            if constexpr (kRow == 2) {
+                off = rel0 + k * 64 + lane;
+                lo = __builtin_amdgcn_readfirstlane(base_lo);
+                hi = __builtin_amdgcn_readfirstlane(base_hi);
+            } else if constexpr (kRow == 1) {
+                const uint32_t rel = rel0 + k * 64;
+                const uint32_t j = (uint32_t)(((uint64_t)rel * w.magic) >> 32);
+                off = rel - j * w.segv + lane;
+                lo = __builtin_amdgcn_readlane(base_lo, j);
+                hi = __builtin_amdgcn_readlane(base_hi, j);
+            } else {
+                const uint32_t rel = rel0 + k * 64 + lane;
+                const uint32_t j = __umulhi(rel, w.magic);
+                off = rel - j * w.segv;
+                lo = __builtin_amdgcn_ds_bpermute(j << 2, base_lo);
+                hi = __builtin_amdgcn_ds_bpermute(j << 2, base_hi);
             }
-            if constexpr (kTwo) {
-                const int32_t b1 = rows1[s];
-                if (blk_ok(p, b1)) {
-                    v4u *d = reinterpret_cast<v4u *>(dst_plane + (int64_t)b1 * p.block_stride) + tid;
+            v4u *base = reinterpret_cast<v4u *>(((uint64_t)hi << 32) | lo);
+            return base && v0 + k * 64 + lane < w.slotv ? base + off : nullptr;
+        };
+        v4u *stg = reinterpret_cast<v4u *>(p.staging + (int64_t)jb.x * p.slot_bytes) + v0 + lane;
+        v4u r[V];
+        if constexpr (kMode == kWinStore) {
+            uint32_t copied = 0;
 #pragma unroll
-                    for (int x = 0; x < V; ++x) __builtin_nontemporal_store(A[x], d + x * T);
+            for (int k = 0; k < V; ++k)
+                if (const v4u *src = paged(k)) {
+                    copied |= 1u << k;
+                    r[k] = __builtin_nontemporal_load(src);
                 }
-            }
-        }
-        if (s + 1 >= ns) break;
-        const int32_t s2 = s + 2 < ns ? s + 2 : ns - 1;
-        const v4u *n2 = reinterpret_cast<const v4u *>(src + (int64_t)s2 * seg) + tid;
 #pragma unroll
-        for (int x = 0; x < V; ++x) A[x] = n2[x * T];
-        {
-            const int32_t b0 = rows0[s + 1];
-            if (blk_ok(p, b0)) {
-                v4u *d = reinterpret_cast<v4u *>(dst_plane + (int64_t)b0 * p.block_stride) + tid;
-#pragma unroll
-                for (int x = 0; x < V; ++x) __builtin_nontemporal_store(B[x], d + x * T);
-            }
-            if constexpr (kTwo) {
-                const int32_t b1 = rows1[s + 1];
-                if (blk_ok(p, b1)) {
-                    v4u *d = reinterpret_cast<v4u *>(dst_plane + (int64_t)b1 * p.block_stride) + tid;
-#pragma unroll
-                    for (int x = 0; x < V; ++x) __builtin_nontemporal_store(B[x], d + x * T);
-                }
-            }
-        }
-    }
-}
-
-template <int R>
-__global__ __launch_bounds__(256) void retrieve_pair_kernel(CopyParams p) {
-    const int tid = threadIdx.x;
-    const int64_t npair = ((int64_t)p.num_jobs + 1) / 2;
-    const int64_t units = npair * p.L * 2;
-    const int64_t per_xcd = (units + kXcds - 1) / kXcds;
-    const const_job_ptr jobs = (const_job_ptr)p.jobs;
-    // the unit order and XCD ranges of retrieve_unit_kernel, over pairs
-    for (int64_t w = blockIdx.x; w < per_xcd * kXcds; w += gridDim.x) {
-        const int64_t u = (w % kXcds) * per_xcd + w / kXcds;
-        if (u >= units) continue;
-        const int64_t q0 = 2 * (u % npair);
-        const int64_t t = u / npair;
-        const int32_t kv = (int32_t)(t & 1);
-        const int32_t l = (int32_t)(t >> 1);
-        const bool has1 = q0 + 1 < p.num_jobs;
-        const v4i j0 = jobs[q0];
-        const v4i j1 = has1 ? jobs[q0 + 1] : v4i{-1, -1, -1, 0};
-        const bool ok0 = job_ok(p, j0);
-        const bool ok1 = has1 && job_ok(p, j1);
-        char *dst_plane = p.layers[l] + kv * p.kv_stride;
-        const int64_t plane_off = ((int64_t)l * 2 + kv) * p.nseg * p.seg_bytes;
-        const const_i32_ptr rows0 = (const_i32_ptr)p.bt + (ok0 ? (int64_t)j0.y * p.bt_stride + (int64_t)j0.z * p.nseg : 0);
-        const const_i32_ptr rows1 = (const_i32_ptr)p.bt + (ok1 ? (int64_t)j1.y * p.bt_stride + (int64_t)j1.z * p.nseg : 0);
-        if (ok0 && ok1 && j0.x == j1.x) {
-            pair_walk<R, true>(p, p.staging + (int64_t)j0.x * p.slot_bytes + plane_off, rows0, rows1, dst_plane, tid);
+            for (int k = 0; k < V; ++k)
+                if ((copied >> k) & 1) __builtin_nontemporal_store(r[k], stg + k * 64);
         } else {
-            if (ok0) pair_walk<R, false>(p, p.staging + (int64_t)j0.x * p.slot_bytes + plane_off, rows0, rows0, dst_plane, tid);
-            if (ok1) pair_walk<R, false>(p, p.staging + (int64_t)j1.x * p.slot_bytes + plane_off, rows1, rows1, dst_plane, tid);
+            // a segment whose block id is invalid is read but not written
+#pragma unroll
+            for (int k = 0; k < V; ++k)
+                if (v0 + k * 64 + lane < w.slotv) r[k] = load16<kMode == kWinStream>(stg + k * 64);
+#pragma unroll
+            for (int k = 0; k < V; ++k)
+                if (v4u *dst = paged(k)) __builtin_nontemporal_store(r[k], dst);
         }
     }
+}
+
+// Large launches: store, streaming retrieve (16 vectors a lane) and the
+// retrieve with shared chunks (4 vectors a lane).
+template <int T, int kRow, bool kRetrieve>
+__global__ __launch_bounds__(T) void group_copy_kernel(CopyParams p, WindowParams w) {
+    copy_window<T, 16, kRetrieve ? kWinStream : kWinStore, kRow>(p, w);
+}
+
+template <int kRow>
+__global__ __launch_bounds__(256) void retrieve_unit_kernel(CopyParams p, WindowParams w) {
+    copy_window<256, 4, kWinShared, kRow>(p, w);
+}
+
+// The same for launches that the memory-side caches or one set of resident
+// waves hold.
+template <int T, int V, WindowMode kMode, int kRow>
+__global__ __launch_bounds__(T) void small_copy_kernel(CopyParams p, WindowParams w) {
+    copy_window<T, V, kMode, kRow>(p, w);
 }
 
 // --------------------------------------------------------------------------
@@ -276,69 +257,6 @@ __global__ __launch_bounds__(1024) void retrieve_quad_kernel(CopyParams p) {
         for (int r = 0; r < R; ++r) a[r] = src[r * T];
 #pragma unroll
         for (int r = 0; r < R; ++r) __builtin_nontemporal_store(a[r], dst + r * T);
-    }
-}
-
-// --------------------------------------------------------------------------
-// Group fast path (store, streaming retrieve): T lanes, R rows of T*16 bytes
-// per segment, SPW segments per workgroup (R * SPW = 16 vectors per lane).
-// --------------------------------------------------------------------------
-template <int T, int R, bool kRetrieve>
-__global__ __launch_bounds__(T) void group_copy_kernel(CopyParams p) {
-    constexpr int SPW = 16 / R;
-    constexpr int V = R * SPW;
-    const int tid = threadIdx.x;
-    const int32_t gpu = (p.nseg + SPW - 1) / SPW;
-    const int64_t total = (int64_t)p.num_jobs * p.L * 2 * gpu;
-    const int64_t per_xcd = (total + kXcds - 1) / kXcds;
-    // XCD x copies the contiguous range [x*per_xcd, (x+1)*per_xcd) of the
-    // job-major group order: whole staging slots per die.
-    for (int64_t w = blockIdx.x; w < per_xcd * kXcds; w += gridDim.x) {
-        const int64_t g = (w % kXcds) * per_xcd + w / kXcds;
-        if (g >= total) continue;
-        const int32_t ig = (int32_t)(g % gpu);
-        int64_t t = g / gpu;
-        const int32_t kv = (int32_t)(t & 1);
-        t >>= 1;
-        const int32_t l = (int32_t)(t % p.L);
-        const int64_t q = t / p.L;
-        const v4i jb = ((const_job_ptr)p.jobs)[q];
-        if (!job_ok(p, jb)) continue;
-        const int32_t s0 = ig * SPW;
-        const const_i32_ptr btp = (const_i32_ptr)p.bt + (int64_t)jb.y * p.bt_stride + (int64_t)jb.z * p.nseg + s0;
-        int32_t blk[SPW];
-#pragma unroll
-        for (int j = 0; j < SPW; ++j) blk[j] = (s0 + j < p.nseg) ? btp[j] : -1;
-        char *plane = p.layers[l] + kv * p.kv_stride;
-        v4u *stg = reinterpret_cast<v4u *>(p.staging + (int64_t)jb.x * p.slot_bytes +
-                                           (((int64_t)l * 2 + kv) * p.nseg + s0) * p.seg_bytes) + tid;
-        v4u r[V];
-        if constexpr (kRetrieve) {
-            // staged segments s0.. are contiguous; a segment whose block id is invalid is read but not written
-#pragma unroll
-            for (int k = 0; k < V; ++k)
-                if (s0 + k / R < p.nseg) r[k] = __builtin_nontemporal_load(stg + (int64_t)k * T);
-#pragma unroll
-            for (int k = 0; k < V; ++k) {
-                const int j = k / R;
-                if (blk_ok(p, blk[j])) {
-                    v4u *dst = reinterpret_cast<v4u *>(plane + (int64_t)blk[j] * p.block_stride) + tid;
-                    __builtin_nontemporal_store(r[k], dst + (k % R) * T);
-                }
-            }
-        } else {
-#pragma unroll
-            for (int k = 0; k < V; ++k) {
-                const int j = k / R;
-                if (blk_ok(p, blk[j])) {
-                    const v4u *src = reinterpret_cast<const v4u *>(plane + (int64_t)blk[j] * p.block_stride) + tid;
-                    r[k] = __builtin_nontemporal_load(src + (k % R) * T);
-                }
-            }
-#pragma unroll
-            for (int k = 0; k < V; ++k)
-                if (blk_ok(p, blk[k / R])) __builtin_nontemporal_store(r[k], stg + (int64_t)k * T);
-        }
     }
 }
 
@@ -395,19 +313,120 @@ constexpr int64_t kMaxGrid = int64_t(1) << 30;
 
 unsigned grid_of(int64_t items) { return (unsigned)(items < kMaxGrid ? items : kMaxGrid); }
 
-template <int R>
-void launch_retrieve_unit(const CopyParams &p, hipStream_t s) {
-    const int64_t units = (int64_t)p.num_jobs * p.L * 2;
-    const int64_t grid = (units + kXcds - 1) / kXcds * kXcds;   // kMaxGrid is a multiple of kXcds too
-    hipLaunchKernelGGL(retrieve_unit_kernel<R>, dim3(grid_of(grid)), dim3(256), 0, s, p);
+// Workgroups of a launch: one per item, at most 2^31 work-items (the rest by the kernels' grid-stride loops).
+template <int T>
+unsigned window_grid(uint32_t total) {
+    const uint32_t grid = (total + kXcds - 1) / kXcds * kXcds;
+    constexpr uint32_t cap = (1u << 31) / T;
+    return grid < cap ? grid : cap;
 }
 
-template <int T, int R, bool kRetrieve>
-void launch_group(const CopyParams &p, hipStream_t s) {
-    const int64_t gpu = (p.nseg + 16 / R - 1) / (16 / R);
-    const int64_t total = (int64_t)p.num_jobs * p.L * 2 * gpu;
-    hipLaunchKernelGGL((group_copy_kernel<T, R, kRetrieve>), dim3(grid_of((total + kXcds - 1) / kXcds * kXcds)),
-                       dim3(T), 0, s, p);
+// Parameters of a window copy with T * V vectors per workgroup.  False where
+// the window copy does not apply (segment size, or counts beyond 31 bits).
+bool window_params(const CopyParams &p, int64_t wg_vectors, int64_t group, WindowParams &w) {
+    if (p.seg_bytes < kMinWindowSeg || p.seg_bytes > kMaxWindowSeg) return false;
+    const int64_t slotv = p.slot_bytes / 16;
+    const int64_t nwg = ((slotv + wg_vectors - 1) / wg_vectors + group - 1) / group * group;
+    // vector indexes of a window that starts before the slot's end stay below 2^32
+    if (slotv > (int64_t(1) << 30) || nwg * p.num_jobs >= (int64_t(1) << 31) - kXcds) return false;
+    w.segv = (uint32_t)(p.seg_bytes / 16);
+    w.slotv = (uint32_t)slotv;
+    w.nsegs = (uint32_t)(slotv / w.segv);
+    w.magic = (uint32_t)(((uint64_t(1) << 32) + w.segv - 1) / w.segv);
+    w.nwg = (uint32_t)nwg;
+    w.group = (uint32_t)group;
+    return true;
+}
+
+// kRow of a launch with windows of `window` bytes: see copy_window.
+int row_class(const CopyParams &p, int64_t window) {
+    return p.seg_bytes % window == 0 ? 2 : p.seg_bytes % 1024 == 0 ? 1 : 0;
+}
+
+#define TKV_LAUNCH_WINDOW(T, kernel)                                                                          \
+    hipLaunchKernelGGL((kernel), dim3(window_grid<T>((uint32_t)p.num_jobs * w.nwg)), dim3(T), 0, s, p, w)
+
+template <int T, bool kRetrieve>
+bool launch_group(const CopyParams &p, hipStream_t s) {
+    WindowParams w;
+    if (!window_params(p, T * 16, 1, w)) return false;
+    switch (row_class(p, 16 << 10)) {
+    case 2: TKV_LAUNCH_WINDOW(T, (group_copy_kernel<T, 2, kRetrieve>)); break;
+    case 1: TKV_LAUNCH_WINDOW(T, (group_copy_kernel<T, 1, kRetrieve>)); break;
+    default: TKV_LAUNCH_WINDOW(T, (group_copy_kernel<T, 0, kRetrieve>)); break;
+    }
+    return true;
+}
+
+bool launch_unit(const CopyParams &p, int64_t group, hipStream_t s) {
+    WindowParams w;
+    if (!window_params(p, 256 * 4, group, w)) return false;
+    if (p.seg_bytes % 1024 == 0)
+        TKV_LAUNCH_WINDOW(256, (retrieve_unit_kernel<1>));
+    else
+        TKV_LAUNCH_WINDOW(256, (retrieve_unit_kernel<0>));
+    return true;
+}
+
+template <int T, int V, WindowMode kMode>
+bool launch_small(const CopyParams &p, int64_t group, hipStream_t s) {
+    WindowParams w;
+    if (!window_params(p, T * V, group, w)) return false;
+    if (p.seg_bytes % 1024 == 0)
+        TKV_LAUNCH_WINDOW(T, (small_copy_kernel<T, V, kMode, 1>));
+    else
+        TKV_LAUNCH_WINDOW(T, (small_copy_kernel<T, V, kMode, 0>));
+    return true;
+}
+
+#undef TKV_LAUNCH_WINDOW
+
+// Store and streaming retrieve, by payload.  Median us over rotating buffers,
+// 32 KiB segments unless noted, store / retrieve:
+//   payload      2 KiB a wave    8 KiB          16 KiB, T=512   16 KiB, T=1024
+//   8 MiB (4K)     6.0 /   5.8    8.1 /   6.4    12.2 /  11.3     13.6 /  14.0
+//   32 MiB        14.7 /  14.3   13.3 /  13.6    16.9 /  14.7     18.4 /  17.5
+//   96 MiB        36.7 /  37.0   37.7 /  40.9    33.4 /  35.0     41.9 /  42.6
+//   128 MiB       49.4 /  46.7   54.8 /  55.5    53.4 /  57.6     48.6 /  53.1
+//   512 MiB        182 /   183    203 /   207     199 /   209      197 /   204
+//   8 GiB         2968 /  3147      -            2912 /  3164     2889 /  3131
+//   8 GiB (64K)   2780 /  2875      -            2791 /  2754     2743 /  2695
+// A CU holds 24 waves of the 16 KiB shape and 32 of the 8 KiB one: payloads up
+// to 96 MiB and up to 48 MiB run as one full set of resident waves, which beats
+// many short ones; otherwise short waves win until the launch is long enough
+// for its start and end not to matter.  (A large streaming retrieve of segments
+// below 16 KiB runs 256-lane workgroups: 796 against 792 us with 1024 lanes at
+// 2 GiB of 4 KiB segments; the store keeps 1024: 738 against 745 us.)
+template <bool kRetrieve>
+bool launch_stream(const CopyParams &p, hipStream_t s) {
+    constexpr WindowMode kMode = kRetrieve ? kWinStream : kWinStore;
+    const double payload = (double)p.slot_bytes * p.num_jobs;
+    constexpr double kMiB = 1 << 20;
+    if (payload > 1024 * kMiB)
+        return kRetrieve && p.seg_bytes < 16384 ? launch_group<256, kRetrieve>(p, s) : launch_group<1024, kRetrieve>(p, s);
+    if (payload > 96 * kMiB || payload <= 24 * kMiB) return launch_small<256, 2, kMode>(p, 1, s);
+    if (payload > 48 * kMiB) return launch_small<512, 16, kMode>(p, 1, s);
+    return launch_small<256, 8, kMode>(p, 1, s);
+}
+
+// Retrieve with shared chunks.  Groups of one plane's bytes (at least 512 KiB
+// = 32 workgroups): median ms by workgroups a group, 4 KiB a wave, 8 requests
+// per chunk:
+//   segment   1      8      32     64    (before)
+//   4 KiB    1.08   0.98   0.93   0.94    0.99
+//   16 KiB   2.11   1.95   1.58   1.59    2.29
+//   20 KiB   1.68   1.67   1.60   1.60    2.07   (ragged sharing)
+//   32 KiB   3.90   3.81   3.12   3.10    3.16
+//   64 KiB   4.65   3.82   3.77   3.46    3.62
+// Below, the pieces of a block are written far apart in time; 2 KiB and 8 KiB
+// a wave are 5-40 % slower at these sizes.  A launch that writes up to 640 MiB
+// in segments below 32 KiB is the exception: it lives in the caches, and 2 KiB
+// a wave in groups of 4 is faster (512 MiB of 4 KiB segments: 90 against 104
+// us; 640 MiB of 20 KiB ones: 114 against 129 us).
+bool launch_shared(const CopyParams &p, hipStream_t s) {
+    const double payload = (double)p.slot_bytes * p.num_jobs;
+    if (payload <= (640 << 20) && p.seg_bytes < 32768) return launch_small<256, 2, kWinShared>(p, 4, s);
+    return launch_unit(p, p.seg_bytes * p.nseg > (512 << 10) ? 64 : 32, s);
 }
 
 // Rows of `row_bytes` per segment if the segment is 1, 2, 4, 8 or 16 rows.
@@ -415,14 +434,6 @@ int rows_of(int64_t seg_bytes, int64_t row_bytes) {
     if (seg_bytes % row_bytes) return 0;
     const int64_t r = seg_bytes / row_bytes;
     return (r == 1 || r == 2 || r == 4 || r == 8 || r == 16) ? (int)r : 0;
-}
-
-bool launch_retrieve_pair(const CopyParams &p, hipStream_t s) {
-    if (rows_of(p.seg_bytes, 256 * 16) != 8) return false;   // measured at 32 KiB segments only
-    const int64_t units = ((int64_t)p.num_jobs + 1) / 2 * p.L * 2;
-    const int64_t grid = (units + kXcds - 1) / kXcds * kXcds;
-    hipLaunchKernelGGL(retrieve_pair_kernel<8>, dim3(grid_of(grid)), dim3(256), 0, s, p);
-    return true;
 }
 
 template <int R>
@@ -442,46 +453,16 @@ bool launch_retrieve_quad(const CopyParams &p, hipStream_t s) {
     }
 }
 
-bool launch_retrieve_fast(const CopyParams &p, hipStream_t s) {
-    switch (rows_of(p.seg_bytes, 256 * 16)) {
-    case 1: launch_retrieve_unit<1>(p, s); return true;
-    case 2: launch_retrieve_unit<2>(p, s); return true;
-    case 4: launch_retrieve_unit<4>(p, s); return true;
-    case 8: launch_retrieve_unit<8>(p, s); return true;
-    case 16: launch_retrieve_unit<16>(p, s); return true;
-    default: return false;
-    }
-}
-
-template <int T, bool kRetrieve>
-bool launch_group_t(const CopyParams &p, hipStream_t s) {
-    switch (rows_of(p.seg_bytes, (int64_t)T * 16)) {
-    case 1: launch_group<T, 1, kRetrieve>(p, s); return true;
-    case 2: launch_group<T, 2, kRetrieve>(p, s); return true;
-    case 4: launch_group<T, 4, kRetrieve>(p, s); return true;
-    case 8: launch_group<T, 8, kRetrieve>(p, s); return true;
-    case 16: launch_group<T, 16, kRetrieve>(p, s); return true;
-    default: return false;
-    }
-}
-
-template <bool kRetrieve>
-bool launch_group_fast(const CopyParams &p, hipStream_t s) {
-    return launch_group_t<1024, kRetrieve>(p, s) || launch_group_t<512, kRetrieve>(p, s) ||
-           launch_group_t<256, kRetrieve>(p, s);
-}
-
 }  // namespace
 
 hipError_t launch_copy(const CopyParams &p, CopyKind kind, hipStream_t stream) {
     if (p.total_segs <= 0) return hipSuccess;
     (void)hipGetLastError();   // clear an error left by an unrelated earlier call
     const bool retrieve = kind != kStore;
-    const bool fast = kind == kRetrieve         ? launch_retrieve_fast(p, stream)
-                      : kind == kRetrievePair   ? launch_retrieve_pair(p, stream) || launch_retrieve_fast(p, stream)
-                      : kind == kRetrieveQuad   ? launch_retrieve_quad(p, stream)
-                      : kind == kRetrieveStream ? launch_group_fast<true>(p, stream)
-                                                : launch_group_fast<false>(p, stream);
+    const bool fast = kind == kRetrieve         ? launch_shared(p, stream)
+                      : kind == kRetrieveQuad   ? launch_retrieve_quad(p, stream) || launch_shared(p, stream)
+                      : kind == kRetrieveStream ? launch_stream<true>(p, stream)
+                                                : launch_stream<false>(p, stream);
     if (!fast) {
         const unsigned grid = grid_of(p.total_segs);
         if (retrieve)

@@ -56,8 +56,8 @@ int kv_retrieve_plan(const kv_layout *layout, const kv_job *h_jobs, int32_t num_
         for (int32_t i = 0; i < num_jobs && distinct; ++i) distinct = seen.insert(h_jobs[i].slot).second;
         if (distinct) return KV_RETRIEVE_STREAM;
     }
-    // Pairs pay off when most pairs share their chunk and groups are small
-    // (many groups in flight per XCD); measured at 32 KiB segments.
+    // Lists in which most pairs share their chunk and groups are small.  The
+    // copy that runs is the same for PAIR and UNIT.
     const int64_t seg = (int64_t)layout->block_size * layout->kv_heads * layout->head_dim * layout->elem_bytes;
     if (seg == 32768 && 20 * pairs_shared >= 9 * (int64_t)num_jobs && num_jobs <= 16 * runs)
         return KV_RETRIEVE_PAIR;

@@ -33,13 +33,12 @@ struct CopyParams {
 };
 
 // Which copy a launch performs.  The retrieve kinds move the same bytes:
-// kRetrieve walks one (job, layer, plane) unit per workgroup, reading staged
-// units through the caches; kRetrievePair walks pairs of jobs and reads a
-// unit once for two jobs that share it; kRetrieveStream streams the staged
-// units with non-temporal loads in the store's workgroup shape, for job lists
-// that read each chunk once; kRetrieveQuad copies one segment of four
-// consecutive jobs per 1024-lane workgroup.
-enum CopyKind { kRetrieve, kRetrievePair, kRetrieveStream, kRetrieveQuad, kStore };
+// kRetrieve orders the windows so that jobs sharing a staged chunk read it
+// through one L2; kRetrieveStream streams the staged chunks with non-temporal
+// loads in the store's shape, for job lists that read each chunk once;
+// kRetrieveQuad copies one segment of four consecutive jobs per 1024-lane
+// workgroup.
+enum CopyKind { kRetrieve, kRetrieveStream, kRetrieveQuad, kStore };
 
 // Launchers (copy.hip, hash.hip).  Return hipSuccess or the launch error.
 hipError_t launch_copy(const CopyParams &p, CopyKind kind, hipStream_t stream);

@@ -150,9 +150,7 @@ int kv_retrieve_pipelined(kv_pipeline *pl, const kv_layout *layout, const void *
         pb.jobs = d_jobs + q0;
         pb.num_jobs = q1 - q0;
         pb.total_segs = (int64_t)pb.num_jobs * p.L * 2 * p.nseg;
-        const tkv::CopyKind ck = kind == KV_RETRIEVE_STREAM ? tkv::kRetrieveStream
-                                 : kind == KV_RETRIEVE_PAIR ? tkv::kRetrievePair
-                                                            : tkv::kRetrieve;
+        const tkv::CopyKind ck = kind == KV_RETRIEVE_STREAM ? tkv::kRetrieveStream : tkv::kRetrieve;
         if (tkv::launch_copy(pb, ck, (hipStream_t)stream) != hipSuccess) return KV_EHIP;
         q0 = q1;
     }
