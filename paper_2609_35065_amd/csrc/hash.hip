@@ -4,8 +4,14 @@
 // over the 16 tokens of block b, M = SplitMix64's finalizer.  The digests are
 // independent and computed one block per lane; the chain is sequential, so
 // its latency sets the rate: it runs on the scalar ALU of one wave per
-// request (a step is ~20 scalar instructions: two xor-shift-multiply rounds
-// on 32-bit halves), while the workgroup's other waves digest the next tile.
+// request.  One wave issues at most one instruction every four cycles, so what
+// counts is how many it issues per block: 19 scalar ones (two 64-bit multiplies
+// of six 32-bit instructions each, three xor-shifts, the xor with the digest),
+// two v_readlane for the digest and, in the last tile of a request, two
+// v_writelane for the hash.  In the tiles before it the chain keeps only every
+// eighth hash and the workgroup's other waves, which also digest the next
+// tile, compute the seven between, eight blocks to a lane: 4,096 blocks take
+// 163 us (172 us with every hash kept by the chain).
 //
 // Lookup.  One wave per request probes up to 64 chunk keys at once in the
 // device open-addressing table and turns the 64 hit flags into the length of
@@ -43,13 +49,21 @@ __device__ __forceinline__ uint32_t writelane(uint32_t old, uint32_t val) {
 // Steps K..K+7 of the chain over a full group of 64 blocks, unrolled so that
 // every lane number is an immediate.  The eight digests are read into scalar
 // registers before the eight dependent steps, keeping v_readlane latency off
-// the chain.
-template <int K>
+// the chain.  kAll: lane K+j takes hash K+j; otherwise lane K/8 takes the hash
+// before step K.  The last group of a request has `left` blocks; up to seven
+// steps past them run on whatever the tile holds there and are not stored (62
+// blocks: 5.1 us; 7.3 us as a loop of single steps with lane numbers in registers).
+template <bool kAll, int K>
 struct ChainGroup {
-    static __device__ __forceinline__ void run(uint64_t &h, uint64_t d, uint32_t &lo, uint32_t &hi) {
+    static __device__ __forceinline__ void run(uint64_t &h, uint64_t d, uint32_t &lo, uint32_t &hi, int left) {
+        if (kAll && K > 0 && K >= left) return;
         uint64_t dk[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) dk[j] = readlane64(d, K + j);
+        if constexpr (!kAll) {
+            lo = writelane<K / 8>(lo, (uint32_t)h);
+            hi = writelane<K / 8>(hi, (uint32_t)(h >> 32));
+        }
         __builtin_amdgcn_sched_barrier(0);   // keep the reads ahead of the steps
         uint64_t hk[8];
 #pragma unroll
@@ -57,8 +71,8 @@ struct ChainGroup {
             h = mix64(h ^ dk[j]);
             hk[j] = h;
         }
-        Park<K, 0>::run(hk, lo, hi);
-        ChainGroup<K + 8>::run(h, d, lo, hi);
+        if constexpr (kAll) Park<K, 0>::run(hk, lo, hi);
+        ChainGroup<kAll, K + 8>::run(h, d, lo, hi, left);
     }
     template <int B, int J>
     struct Park {
@@ -73,9 +87,9 @@ struct ChainGroup {
         static __device__ __forceinline__ void run(const uint64_t *, uint32_t &, uint32_t &) {}
     };
 };
-template <>
-struct ChainGroup<64> {
-    static __device__ __forceinline__ void run(uint64_t &, uint64_t, uint32_t &, uint32_t &) {}
+template <bool kAll>
+struct ChainGroup<kAll, 64> {
+    static __device__ __forceinline__ void run(uint64_t &, uint64_t, uint32_t &, uint32_t &, int) {}
 };
 
 __device__ __forceinline__ uint64_t block_digest(const int32_t *tp) {
@@ -88,15 +102,18 @@ __device__ __forceinline__ uint64_t block_digest(const int32_t *tp) {
 // One 256-lane workgroup per request, blocks in tiles of 256.  The digests
 // of a tile are independent: all four waves compute the first tile into LDS;
 // afterwards wave 0 runs the chain over tile t while waves 1-3 digest tile
-// t+1 into the other LDS buffer.  The chain runs with wave-uniform values, so
-// it executes on the scalar ALU: for each group of 64 blocks, lane k holds
-// digest k, v_readlane moves it to scalar registers, and v_writelane parks
-// h_k in lane k, which then stores the group's 64 hashes in one write.
+// t+1 into another LDS buffer and wave 1 fills in the hashes of tile t-1 from
+// every eighth one.  The chain runs with wave-uniform values, so it executes on
+// the scalar ALU: for each group of 64 blocks, lane k holds digest k and
+// v_readlane moves it to scalar registers.  In the last tile v_writelane parks
+// h_k in lane k, which then stores the group's 64 hashes in one write, so that
+// nothing is left to do when the chain ends.
 __global__ __launch_bounds__(kHashThreads) void hash_kernel(const int32_t *__restrict__ tokens,
                                                            const int64_t *__restrict__ tok_off, uint64_t seed,
                                                            const int64_t *__restrict__ blk_off,
                                                            uint64_t *__restrict__ out) {
-    __shared__ uint64_t dig[2][kHashThreads];
+    __shared__ uint64_t dig[3][kHashThreads];
+    __shared__ uint64_t every8[2][kHashThreads / 8];
     const int r = blockIdx.x;
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);   // wave-uniform by construction
@@ -112,35 +129,46 @@ __global__ __launch_bounds__(kHashThreads) void hash_kernel(const int32_t *__res
 
     if (tid < nb) dig[0][tid] = block_digest(tk + (int64_t)tid * 16);
     __syncthreads();
+    if (wave == 0) __builtin_amdgcn_s_setprio(3);   // the chain issues before the waves that share its SIMD
     uint64_t h = seed;   // live in wave 0 only
+    int cur = 0;         // t mod 3
     for (int64_t t = 0; t < ntiles; ++t) {
         const int64_t tb = t * kHashThreads;
+        const int next = cur == 2 ? 0 : cur + 1, prev = cur == 0 ? 2 : cur - 1;
         if (wave == 0) {
-            const uint64_t *dt = dig[t & 1];
-            const int64_t left = nb - tb < kHashThreads ? nb - tb : kHashThreads;
-            for (int64_t g = 0; g < left; g += kWave) {
-                const uint64_t d = dt[g + lane];
-                uint32_t mine_lo = 0, mine_hi = 0;
-                if (left - g >= kWave) {
-                    ChainGroup<0>::run(h, d, mine_lo, mine_hi);
-                } else {                               // ragged last group
-                    const int cnt = (int)(left - g);
-                    uint64_t mine = 0;
-                    for (int k = 0; k < cnt; ++k) {
-                        h = mix64(h ^ readlane64(d, k));
-                        if (lane == k) mine = h;
-                    }
-                    mine_lo = (uint32_t)mine;
-                    mine_hi = (uint32_t)(mine >> 32);
+            const uint64_t *dt = dig[cur];
+            if (t + 1 < ntiles) {                      // a full tile
+                for (int g = 0; g < kHashThreads; g += kWave) {
+                    uint32_t lo = 0, hi = 0;
+                    ChainGroup<false, 0>::run(h, dt[g + lane], lo, hi, kWave);
+                    if (lane < 8) every8[t & 1][g / 8 + lane] = ((uint64_t)hi << 32) | lo;
                 }
-                if (g + lane < left) out[o0 + tb + g + lane] = ((uint64_t)mine_hi << 32) | mine_lo;
+            } else {
+                const int left = (int)(nb - tb);
+                for (int g = 0; g < left; g += kWave) {
+                    uint32_t mine_lo = 0, mine_hi = 0;
+                    ChainGroup<true, 0>::run(h, dt[g + lane], mine_lo, mine_hi, left - g);
+                    if (g + lane < left) out[o0 + tb + g + lane] = ((uint64_t)mine_hi << 32) | mine_lo;
+                }
             }
-        } else if (t + 1 < ntiles) {
-            const int64_t nt = tb + kHashThreads;
-            for (int i = tid - kWave; i < kHashThreads; i += kHashThreads - kWave)
-                if (nt + i < nb) dig[(t + 1) & 1][i] = block_digest(tk + (nt + i) * 16);
+        } else {
+            if (t + 1 < ntiles) {
+                const int64_t nt = tb + kHashThreads;
+                for (int i = tid - kWave; i < kHashThreads; i += kHashThreads - kWave)
+                    if (nt + i < nb) dig[next][i] = block_digest(tk + (nt + i) * 16);
+            }
+            if (t > 0 && wave == 1 && lane < kHashThreads / 8) {   // tile t-1, a full one
+                uint64_t hb = every8[(t - 1) & 1][lane];
+                uint64_t *o = out + o0 + tb - kHashThreads + lane * 8;
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    hb = mix64(hb ^ dig[prev][lane * 8 + k]);
+                    o[k] = hb;
+                }
+            }
         }
         __syncthreads();
+        cur = next;
     }
 }
 
