@@ -11,6 +11,7 @@ from __future__ import annotations
 
 import ctypes as ct
 import os
+from array import array
 from typing import List, Optional, Sequence, Tuple
 
 import numpy as np
@@ -176,9 +177,29 @@ def _check(rc: int, what: str) -> int:
 # marshalling helpers
 # ---------------------------------------------------------------------------
 
+# A small copy takes 10-20 us on the GPU, so what a call costs on the host
+# (32 layer tensors to check, a stream to find) shows: the checks below are
+# those of a plain loop over is_cuda, is_contiguous and data_ptr, run by map()
+# over the C accessors.
+
+def _torch():
+    """The torch module, imported at the first call that needs it."""
+    global _torch_mod
+    if _torch_mod is None:
+        import torch
+        _torch_mod = torch
+    return _torch_mod
+
+
+_torch_mod = None
+
+
 def _stream(stream) -> int:
     if stream is None:
-        import torch
+        torch = _torch()
+        if torch.cuda.is_initialized():
+            # the handle alone, without a Stream object around it
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
         return stream
@@ -189,7 +210,6 @@ def _dptr(t, dtype=None, what: str = "tensor") -> int:
     """Device pointer of a contiguous CUDA (HIP) tensor, or an int address."""
     if isinstance(t, int):
         return t
-    import torch
     if not t.is_cuda:
         raise ValueError(f"{what} must be a device tensor")
     if not t.is_contiguous():
@@ -197,6 +217,11 @@ def _dptr(t, dtype=None, what: str = "tensor") -> int:
     if dtype is not None and t.dtype != dtype:
         raise ValueError(f"{what} must be {dtype}, got {t.dtype}")
     return t.data_ptr()
+
+
+def _hdata(a: np.ndarray) -> int:
+    """Address of an array's data (as a.ctypes.data, at a third of its cost)."""
+    return ct.addressof(ct.c_char.from_buffer(a)) if a.size and a.flags.writeable else a.ctypes.data
 
 
 def make_layout(num_layers: int, kv_heads: int, head_dim: int, elem_bytes: int, block_size: int,
@@ -211,7 +236,7 @@ def make_layout(num_layers: int, kv_heads: int, head_dim: int, elem_bytes: int, 
 # ---------------------------------------------------------------------------
 
 def kv_hash_prefix(d_tokens, d_tok_off, num_reqs: int, seed: int, d_blk_off, d_block_hash, stream=None) -> None:
-    import torch
+    torch = _torch()
     _check(lib().kv_hash_prefix(_dptr(d_tokens, torch.int32, "tokens"), _dptr(d_tok_off, torch.int64, "tok_off"),
                                 num_reqs, seed & 0xFFFFFFFFFFFFFFFF, _dptr(d_blk_off, torch.int64, "blk_off"),
                                 _hash_ptr(d_block_hash), _stream(stream)), "kv_hash_prefix")
@@ -221,7 +246,7 @@ def _hash_ptr(t) -> int:
     """Block hashes are 64-bit words; an int64 (or uint64) tensor holds them."""
     if isinstance(t, int):
         return t
-    import torch
+    torch = _torch()
     if t.dtype not in (torch.int64, getattr(torch, "uint64", torch.int64)):
         raise ValueError(f"block_hash must be a 64-bit integer tensor, got {t.dtype}")
     return _dptr(t, None, "block_hash")
@@ -276,7 +301,7 @@ def kv_index_insert(idx: KvIndex, keys: np.ndarray, slots: np.ndarray, stream=No
     slots = np.ascontiguousarray(slots, np.int32)
     if keys.size != slots.size:
         raise ValueError("keys and slots differ in length")
-    _check(lib().kv_index_insert(idx.handle, keys.ctypes.data, slots.ctypes.data, keys.size, _stream(stream)),
+    _check(lib().kv_index_insert(idx.handle, _hdata(keys), _hdata(slots), keys.size, _stream(stream)),
            "kv_index_insert")
 
 
@@ -295,7 +320,7 @@ def kv_index_insert_static(idx: KvIndex, keys: np.ndarray, slots: np.ndarray, st
 
 def kv_index_erase(idx: KvIndex, keys: np.ndarray, stream=None) -> None:
     keys = np.ascontiguousarray(keys, np.uint64)
-    _check(lib().kv_index_erase(idx.handle, keys.ctypes.data, keys.size, _stream(stream)), "kv_index_erase")
+    _check(lib().kv_index_erase(idx.handle, _hdata(keys), keys.size, _stream(stream)), "kv_index_erase")
 
 
 def kv_index_size(idx: KvIndex) -> int:
@@ -312,7 +337,7 @@ def kv_index_find(idx: KvIndex, key: int) -> int:
 
 def kv_lookup(idx: KvIndex, d_block_hash, d_blk_off, num_reqs: int, blocks_per_chunk: int, d_chunk_off,
               d_chunk_slot, d_hit_chunks, stream=None) -> None:
-    import torch
+    torch = _torch()
     _check(lib().kv_lookup(idx.handle, _hash_ptr(d_block_hash), _dptr(d_blk_off, torch.int64, "blk_off"),
                            num_reqs, blocks_per_chunk, _dptr(d_chunk_off, torch.int64, "chunk_off"),
                            _dptr(d_chunk_slot, torch.int32, "chunk_slot"),
@@ -334,9 +359,9 @@ def kv_build_jobs(hit_chunks: np.ndarray, chunk_slot: np.ndarray, block_hash: np
     store = np.zeros((max(nchunks, 1), 4), np.int32)
     keys = np.zeros(max(nchunks, 1), np.uint64)
     nr, ns, nd = _i32(0), _i32(0), _i32(0)
-    rc = host_lib().kv_build_jobs(hit.ctypes.data, cs.ctypes.data, bh.ctypes.data, bo.ctypes.data, co.ctypes.data, R,
-                             blocks_per_chunk, fs.ctypes.data if fs.size else None, fs.size, retr.ctypes.data,
-                             ct.byref(nr), store.ctypes.data, keys.ctypes.data, ct.byref(ns), ct.byref(nd))
+    rc = host_lib().kv_build_jobs(_hdata(hit), _hdata(cs), _hdata(bh), _hdata(bo), _hdata(co), R,
+                             blocks_per_chunk, _hdata(fs) if fs.size else None, fs.size, _hdata(retr),
+                             ct.byref(nr), _hdata(store), _hdata(keys), ct.byref(ns), ct.byref(nd))
     if rc < 0 and rc != KV_ENOSPC:
         raise KvError(rc, "kv_build_jobs")
     return retr[:nr.value].copy(), store[:ns.value].copy(), keys[:ns.value].copy(), nd.value, rc
@@ -375,9 +400,9 @@ def kv_decide_claims(hit_chunks: np.ndarray, chunk_slot: np.ndarray, chunk_off: 
         raise ValueError("protected must hold one flag per staging slot")
     dec = np.zeros(max(R, 1), np.int32)
     res = _u64(int(reserved_bytes))
-    _check(host_lib().kv_decide_claims(R, hit.ctypes.data, cs.ctypes.data, co.ctypes.data, u.ctypes.data,
-                                       t.ctypes.data, rq.ctypes.data, int(slot_bytes), int(budget_bytes),
-                                       int(num_slots), prot.ctypes.data, ct.byref(res), dec.ctypes.data),
+    _check(host_lib().kv_decide_claims(R, _hdata(hit), _hdata(cs), _hdata(co), _hdata(u),
+                                       _hdata(t), _hdata(rq), int(slot_bytes), int(budget_bytes),
+                                       int(num_slots), _hdata(prot), ct.byref(res), _hdata(dec)),
            "kv_decide_claims")
     return dec[:R].copy(), prot, res.value
 
@@ -402,10 +427,10 @@ def kv_build_jobs_routed(hit_chunks: np.ndarray, chunk_slot: np.ndarray, block_h
     store = np.zeros((max(nchunks, 1), 4), np.int32)
     keys = np.zeros(max(nchunks, 1), np.uint64)
     nr, no, ns, nd = _i32(0), _i32(0), _i32(0), _i32(0)
-    rc = host_lib().kv_build_jobs_routed(hit.ctypes.data, cs.ctypes.data, bh.ctypes.data, bo.ctypes.data,
-                                         co.ctypes.data, R, blocks_per_chunk, fs.ctypes.data if fs.size else None,
-                                         fs.size, rq.ctypes.data, dec.ctypes.data, retr.ctypes.data, ct.byref(nr),
-                                         ordn.ctypes.data, ct.byref(no), store.ctypes.data, keys.ctypes.data,
+    rc = host_lib().kv_build_jobs_routed(_hdata(hit), _hdata(cs), _hdata(bh), _hdata(bo),
+                                         _hdata(co), R, blocks_per_chunk, _hdata(fs) if fs.size else None,
+                                         fs.size, _hdata(rq), _hdata(dec), _hdata(retr), ct.byref(nr),
+                                         _hdata(ordn), ct.byref(no), _hdata(store), _hdata(keys),
                                          ct.byref(ns), ct.byref(nd))
     if rc < 0 and rc != KV_ENOSPC:
         raise KvError(rc, "kv_build_jobs_routed")
@@ -443,19 +468,22 @@ def kv_ttr_state_aware(objs, obj_bytes, resident, queued, ready_at, now_s: float
     return out.value
 
 
-def _layer_array(layers: Sequence) -> ct.Array:
-    arr = (_vp * len(layers))()
-    for i, t in enumerate(layers):
-        arr[i] = _dptr(t, None, f"layer {i}")
-    return arr
+def _layer_array(layers: Sequence) -> array:
+    """The layers' device pointers (array of 64-bit words, passed by address)."""
+    tensor = _torch().Tensor
+    if all(type(t) is tensor for t in layers) and all(map(tensor.is_cuda.__get__, layers)) \
+            and all(map(tensor.is_contiguous, layers)):
+        return array("Q", map(tensor.data_ptr, layers))
+    return array("Q", [_dptr(t, None, f"layer {i}") for i, t in enumerate(layers)])
 
 
 def kv_retrieve_scatter(layout: KvLayout, d_staging, layers: Sequence, d_block_tables, bt_stride: int,
                         num_reqs: int, d_jobs, num_jobs: int, stream=None) -> None:
-    import torch
+    torch = _torch()
     if len(layers) != layout.num_layers:
         raise ValueError("one paged tensor per layer is required")
-    _check(lib().kv_retrieve_scatter(ct.byref(layout), _dptr(d_staging, None, "staging"), _layer_array(layers),
+    lp = _layer_array(layers)   # alive during the call
+    _check(lib().kv_retrieve_scatter(ct.byref(layout), _dptr(d_staging, None, "staging"), lp.buffer_info()[0],
                                      _dptr(d_block_tables, torch.int32, "block_tables"), bt_stride, num_reqs,
                                      _dptr(d_jobs, torch.int32, "jobs") if num_jobs else None, num_jobs,
                                      _stream(stream)), "kv_retrieve_scatter")
@@ -464,28 +492,30 @@ def kv_retrieve_scatter(layout: KvLayout, d_staging, layers: Sequence, d_block_t
 def kv_retrieve_plan(layout: KvLayout, h_jobs: np.ndarray) -> int:
     """The retrieve variant (KV_RETRIEVE_*) for a job list ([n,4] int32, grouped by slot)."""
     hj = np.ascontiguousarray(h_jobs, np.int32).reshape(-1, 4)
-    return _check(host_lib().kv_retrieve_plan(ct.byref(layout), hj.ctypes.data if hj.size else None, hj.shape[0]),
+    return _check(host_lib().kv_retrieve_plan(ct.byref(layout), _hdata(hj) if hj.size else None, hj.shape[0]),
                   "kv_retrieve_plan")
 
 
 def kv_retrieve_scatter_as(kind: int, layout: KvLayout, d_staging, layers: Sequence, d_block_tables,
                            bt_stride: int, num_reqs: int, d_jobs, num_jobs: int, stream=None) -> None:
     """kv_retrieve_scatter with an explicit variant (KV_RETRIEVE_UNIT / PAIR / STREAM / QUAD)."""
-    import torch
+    torch = _torch()
     if len(layers) != layout.num_layers:
         raise ValueError("one paged tensor per layer is required")
+    lp = _layer_array(layers)   # alive during the call
     _check(lib().kv_retrieve_scatter_as(kind, ct.byref(layout), _dptr(d_staging, None, "staging"),
-                                        _layer_array(layers), _dptr(d_block_tables, torch.int32, "block_tables"),
+                                        lp.buffer_info()[0], _dptr(d_block_tables, torch.int32, "block_tables"),
                                         bt_stride, num_reqs, _dptr(d_jobs, torch.int32, "jobs") if num_jobs else None,
                                         num_jobs, _stream(stream)), "kv_retrieve_scatter_as")
 
 
 def kv_store_gather(layout: KvLayout, d_staging, layers: Sequence, d_block_tables, bt_stride: int,
                     num_reqs: int, d_jobs, num_jobs: int, stream=None) -> None:
-    import torch
+    torch = _torch()
     if len(layers) != layout.num_layers:
         raise ValueError("one paged tensor per layer is required")
-    _check(lib().kv_store_gather(ct.byref(layout), _dptr(d_staging, None, "staging"), _layer_array(layers),
+    lp = _layer_array(layers)   # alive during the call
+    _check(lib().kv_store_gather(ct.byref(layout), _dptr(d_staging, None, "staging"), lp.buffer_info()[0],
                                  _dptr(d_block_tables, torch.int32, "block_tables"), bt_stride, num_reqs,
                                  _dptr(d_jobs, torch.int32, "jobs") if num_jobs else None, num_jobs,
                                  _stream(stream)), "kv_store_gather")
@@ -498,10 +528,11 @@ def kv_probe_mixed_traffic(layout: KvLayout, d_staging, layers: Sequence, d_bloc
     segment of the listed slots and writes `fill` into every destination block of
     the jobs, interleaved in one launch with no data passing between them.
     Overwrites those destination blocks."""
-    import torch
+    torch = _torch()
     if len(layers) != layout.num_layers:
         raise ValueError("one paged tensor per layer is required")
-    _check(lib().kv_probe_mixed_traffic(ct.byref(layout), _dptr(d_staging, None, "staging"), _layer_array(layers),
+    lp = _layer_array(layers)   # alive during the call
+    _check(lib().kv_probe_mixed_traffic(ct.byref(layout), _dptr(d_staging, None, "staging"), lp.buffer_info()[0],
                                         _dptr(d_block_tables, torch.int32, "block_tables"), bt_stride, num_reqs,
                                         _dptr(d_jobs, torch.int32, "jobs") if num_jobs else None, num_jobs,
                                         _dptr(d_slots, torch.int32, "slots") if num_read_slots else None,
@@ -571,17 +602,18 @@ def kv_retrieve_pipelined(pipeline: KvPipeline, layout: KvLayout, h_lower_tier, 
     """Retrieve whose chunks start in the lower tier: per batch of slots,
     DMA copy on copy_stream, then the scatter on `stream` once they landed.
     h_jobs ([n,4] int32, grouped by slot) and d_jobs hold the same jobs."""
-    import torch
+    torch = _torch()
     if len(layers) != layout.num_layers:
         raise ValueError("one paged tensor per layer is required")
+    lp = _layer_array(layers)   # alive during the call
     hj = np.ascontiguousarray(h_jobs, np.int32).reshape(-1, 4)
     n = hj.shape[0]
     if n and (d_jobs is None or int(d_jobs.numel()) != 4 * n):
         raise ValueError("d_jobs must hold the same jobs as h_jobs")
     _check(lib().kv_retrieve_pipelined(pipeline.handle, ct.byref(layout), _hptr(h_lower_tier, "lower tier") if n else None,
-                                       _dptr(d_staging, None, "staging"), _layer_array(layers),
+                                       _dptr(d_staging, None, "staging"), lp.buffer_info()[0],
                                        _dptr(d_block_tables, torch.int32, "block_tables"), bt_stride, num_reqs,
-                                       hj.ctypes.data if n else None,
+                                       _hdata(hj) if n else None,
                                        _dptr(d_jobs, torch.int32, "jobs") if n else None, n, slots_per_batch,
                                        _stream(copy_stream), _stream(stream)), "kv_retrieve_pipelined")
 
@@ -589,7 +621,7 @@ def kv_retrieve_pipelined(pipeline: KvPipeline, layout: KvLayout, h_lower_tier, 
 def kv_group_jobs_by_slot(jobs: np.ndarray) -> np.ndarray:
     """Returns the jobs ([n,4] int32) stably ordered by slot (a copy)."""
     jb = np.ascontiguousarray(jobs, np.int32).reshape(-1, 4).copy()
-    _check(host_lib().kv_group_jobs_by_slot(jb.ctypes.data if jb.size else None, jb.shape[0]), "kv_group_jobs_by_slot")
+    _check(host_lib().kv_group_jobs_by_slot(_hdata(jb) if jb.size else None, jb.shape[0]), "kv_group_jobs_by_slot")
     return jb
 
 

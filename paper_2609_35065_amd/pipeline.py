@@ -170,22 +170,27 @@ class StagingPath:
             self.tok_off = torch.from_numpy(w.tok_off).to(d)
             self.blk_off = torch.from_numpy(blk_off).to(d)
             self.chunk_off = torch.from_numpy(chunk_off).to(d)
-            self.block_hash = torch.empty(max(nblk, 1), dtype=torch.int64, device=d)
-            self.chunk_slot = torch.empty(max(nch, 1), dtype=torch.int32, device=d)
-            self.hit = torch.empty(max(R, 1), dtype=torch.int32, device=d)
+            # the lookup's results lie in one buffer, so that one copy brings them to the host
+            sizes = (8 * max(nblk, 1), 4 * max(nch, 1), 4 * max(R, 1))
+            self._found = torch.empty(sum(sizes), dtype=torch.uint8, device=d)
+            self.block_hash, self.chunk_slot, self.hit = self._result_views(self._found, sizes)
             self.bt = torch.from_numpy(np.ascontiguousarray(w.block_tables)).to(d)
             self.d_retr = torch.empty((max(nch, 1), 4), dtype=torch.int32, device=d)
             self.d_store = torch.empty((max(nch, 1), 4), dtype=torch.int32, device=d)
         # pinned host mirrors for the one D2H and one H2D copy of a pass
-        self.h_block_hash = torch.zeros(max(nblk, 1), dtype=torch.int64, pin_memory=True)
-        self.h_chunk_slot = torch.zeros(max(nch, 1), dtype=torch.int32, pin_memory=True)
-        self.h_hit = torch.zeros(max(R, 1), dtype=torch.int32, pin_memory=True)
+        self._h_found = torch.zeros(sum(sizes), dtype=torch.uint8, pin_memory=True)
+        self.h_block_hash, self.h_chunk_slot, self.h_hit = self._result_views(self._h_found, sizes)
         # job lists, two of each: a pass fills one while the upload of the other may still be queued
         self._h_retr = [torch.zeros((max(nch, 1), 4), dtype=torch.int32, pin_memory=True) for _ in range(2)]
         self._h_store = [torch.zeros((max(nch, 1), 4), dtype=torch.int32, pin_memory=True) for _ in range(2)]
         self._uploaded = [torch.cuda.Event(), torch.cuda.Event()]
         self.stream.synchronize()
         self.lookup_stream.synchronize()
+
+    @staticmethod
+    def _result_views(buf: torch.Tensor, sizes):
+        a, b = sizes[0], sizes[0] + sizes[1]
+        return buf[:a].view(torch.int64), buf[a:b].view(torch.int32), buf[b:].view(torch.int32)
 
     # ------------------------------------------------------------------
     def staging_view(self) -> torch.Tensor:
@@ -288,9 +293,7 @@ class StagingPath:
             kv_lookup(self.index, self.block_hash, self.blk_off, R, self.bpc, self.chunk_off, self.chunk_slot,
                       self.hit, ls)
             self._ev_end(e, ls)
-            self.h_block_hash.copy_(self.block_hash, non_blocking=True)
-            self.h_chunk_slot.copy_(self.chunk_slot, non_blocking=True)
-            self.h_hit.copy_(self.hit, non_blocking=True)
+            self._h_found.copy_(self._found, non_blocking=True)
             self._lookup_done.record(ls)
 
     def default_claims(self) -> ClaimInputs:
@@ -321,9 +324,6 @@ class StagingPath:
         st.ordinary_bytes = len(ordn) * slot_bytes
         st.store_bytes = len(store) * slot_bytes
         st.reserved_bytes = reserved
-        for d, c in zip(*np.unique(dec, return_counts=True)):
-            st.decisions[int(d)] = int(c)
-        st.commits = int(np.count_nonzero(dec == KV_COMMIT))
         if validate:
             from . import kv_validate_jobs
             both = np.concatenate([retr, ordn])
@@ -411,6 +411,10 @@ class StagingPath:
         self.last_store_keys, self.last_store_slots = skeys, store[:, 0].copy()
         self.last_retrieve, self.last_ordinary, self.last_store = retr, ordn, store
         self.last_decisions = dec
+        # counted here, while the copies run
+        for d, c in zip(*np.unique(dec, return_counts=True)):
+            st.decisions[int(d)] = int(c)
+        st.commits = int(np.count_nonzero(dec == KV_COMMIT))
         if evict_stored and ns:
             self.evict_last()
         return st
