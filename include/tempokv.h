@@ -248,9 +248,9 @@ typedef enum kv_retrieve_kind {
     KV_RETRIEVE_QUAD = 3    /* one 1024-lane workgroup per (layer, plane, 4 consecutive jobs, segment): jobs of
                                the window that share a chunk load it together, one read from memory and the
                                rest from L2.  Segments of 4, 8, 16, 32 or 64 KiB (other sizes run as UNIT).
-                               Never returned by kv_retrieve_plan: whether it beats UNIT depends on where the
-                               paged pool lies in physical memory, so a caller picks it by timing both on its
-                               own pool. */
+                               Never returned by kv_retrieve_plan: UNIT was as fast or faster on every pool
+                               last measured, though both depend on where the paged pool lies in physical
+                               memory; a caller may time both on its own pool. */
 } kv_retrieve_kind;
 
 /* Pick the variant for a job list from its host copy (grouped by slot, as

@@ -34,8 +34,9 @@
 //   Loads are cached, paged writes non-temporal.
 //
 // A further retrieve, the four-job-window retrieve (one segment of four
-// consecutive jobs per 1024-lane workgroup), is faster on some pools and
-// slower on others, so the caller picks it by timing.
+// consecutive jobs per 1024-lane workgroup), runs where a caller names it: 3.69
+// to 3.83 ms against 3.18 to 3.65 for the windows at the 32-layer batch on three
+// pools, 1.55 against 0.79 ms at 4 KiB segments.
 //
 // Generic path: any segment size that is a multiple of 16 bytes, one
 // 256-lane workgroup per segment.
