@@ -410,6 +410,16 @@ bool launch_stream(const CopyParams &p, hipStream_t s) {
     return launch_small<256, 8, kMode>(p, 1, s);
 }
 
+// Whether a device-accessible pointer maps host memory (about 1 us on the host).
+bool in_host_memory(const void *ptr) {
+    hipPointerAttribute_t at;
+    if (hipPointerGetAttributes(&at, ptr) != hipSuccess) {
+        (void)hipGetLastError();   // memory that HIP did not allocate
+        return false;
+    }
+    return at.type == hipMemoryTypeHost;
+}
+
 // Retrieve with shared chunks.  Groups of one plane's bytes (at least 512 KiB
 // = 32 workgroups): median ms by workgroups a group, 4 KiB a wave, 8 requests
 // per chunk:
@@ -424,9 +434,14 @@ bool launch_stream(const CopyParams &p, hipStream_t s) {
 // in segments below 32 KiB is the exception: it lives in the caches, and 2 KiB
 // a wave in groups of 4 is faster (512 MiB of 4 KiB segments: 90 against 104
 // us; 640 MiB of 20 KiB ones: 114 against 129 us).
+// Staged chunks in host memory are read through the link, where what counts is
+// that the jobs sharing a chunk read the same bytes at the same time: groups of
+// one (1,024 requests on 48 chunks: 29.3 ms; 31.0 in groups of 8, 33.5 in
+// groups of 32).
 bool launch_shared(const CopyParams &p, hipStream_t s) {
     const double payload = (double)p.slot_bytes * p.num_jobs;
     if (payload <= (640 << 20) && p.seg_bytes < 32768) return launch_small<256, 2, kWinShared>(p, 4, s);
+    if (in_host_memory(p.staging)) return launch_unit(p, 1, s);
     return launch_unit(p, p.seg_bytes * p.nseg > (512 << 10) ? 64 : 32, s);
 }
 

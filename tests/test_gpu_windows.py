@@ -99,3 +99,37 @@ def test_segment_sizes(shape, layout, pad, op):
 @pytest.mark.parametrize("mib", [23, 36, 60, 100, 600, 700, 1030])
 def test_launch_shapes(mib, shape, op):
     _check(shape, mib * MIB, op, "kv_first", 16, 11)
+
+
+@pytest.mark.parametrize("host", [False, True])
+def test_shared_retrieve_captured(host):
+    # The shared retrieve asks where the staged chunks lie before it launches: from device and from host memory,
+    # eager and captured (replayed three times, with eager work and a synchronisation between).
+    lo, pool, staging, bt, jobs, ok, dims = _setup(SHAPES["32k"], 20 * MIB, 0.3, "kv_first", 0, 5)
+    want, _ = _expected(pool, staging, bt, jobs, ok, dims, False)
+    if host:
+        pinned = torch.empty(staging.numel(), dtype=torch.int64, pin_memory=True)
+        pinned.copy_(staging)
+        src = kv.kv_host_device_pointer(pinned.data_ptr())
+    else:
+        src = staging
+    d_bt, d_jobs = torch.from_numpy(bt).cuda(), torch.from_numpy(jobs).cuda()
+    start = [t.clone() for t in pool]
+
+    def run():
+        kv.kv_retrieve_scatter(lo, src, pool, d_bt, bt.shape[1], bt.shape[0], d_jobs, len(jobs))
+
+    def check():
+        torch.cuda.synchronize()
+        for a, b, c in zip(pool, want, start):
+            assert torch.equal(a, b)
+            a.copy_(c)
+
+    run()
+    check()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        run()
+    for _ in range(3):
+        g.replay()
+        check()
