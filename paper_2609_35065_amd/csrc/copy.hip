@@ -14,7 +14,8 @@
 // planes, whatever the segment size.
 //
 // Both directions run copy_window: one wave per window, T/64 consecutive
-// windows per workgroup, all loads of a window before its stores.  What bounds
+// windows of the launch's order (window.h) per workgroup, all loads of a window
+// before its stores.  What bounds
 // a copy is how the memory system takes its order of reads and writes, so the
 // three shapes differ in how much a wave moves and which windows are in flight
 // together:
@@ -42,6 +43,7 @@
 // 256-lane workgroup per segment.
 
 #include "internal.h"
+#include "window.h"
 
 namespace tkv {
 namespace {
@@ -68,10 +70,6 @@ __device__ __forceinline__ bool blk_ok(const CopyParams &p, int32_t blk) {
     return blk >= 0 && blk < p.num_blocks;
 }
 
-// Accelerator complex dies on MI355X; consecutive workgroups of a launch are
-// dispatched to them round-robin.  Only performance depends on this value.
-constexpr int kXcds = 8;
-
 // --------------------------------------------------------------------------
 // Window copy.  Bound by the memory system: ~5.8-6.0 TB/s (read + write) for a
 // large store of 32 KiB segments and 5.3-5.6 TB/s for a retrieve, which is what
@@ -92,18 +90,6 @@ constexpr int kXcds = 8;
 // the index is below segv + 1024 and the bracket below segv, so it holds for
 // segv <= 32768 (kMaxWindowSeg).
 // --------------------------------------------------------------------------
-constexpr int64_t kMinWindowSeg = 512;        // V * 64 vectors touch at most 33 segments: one lane each
-constexpr int64_t kMaxWindowSeg = 512 << 10;
-
-struct WindowParams {
-    uint32_t segv;     // 16-byte vectors of a segment
-    uint32_t slotv;    // ... of a slot
-    uint32_t nsegs;    // segments of a slot
-    uint32_t magic;    // ceil(2^32 / segv)
-    uint32_t nwg;      // workgroups of a slot, a multiple of group
-    uint32_t group;    // consecutive workgroups of one job (shared retrieve)
-};
-
 enum WindowMode { kWinStore, kWinStream, kWinShared };
 
 template <int T, int V, WindowMode kMode, int kRow>
@@ -112,24 +98,14 @@ __device__ __forceinline__ void copy_window(const CopyParams &p, const WindowPar
     constexpr uint32_t W = T / 64;
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t total = (uint32_t)p.num_jobs * w.nwg;   // below 2^31 (window_params)
-    const uint32_t per_xcd = (total + kXcds - 1) / kXcds;
-    // workgroup b runs on XCD b mod 8, so XCD x copies the contiguous range
-    // [x*per_xcd, (x+1)*per_xcd) of the order; the grid is a multiple of kXcds
+    const uint32_t jobs = (uint32_t)p.num_jobs;
+    const uint32_t per_xcd = window_wgs_per_xcd(w.total, W);
     for (uint32_t b = blockIdx.x; b < per_xcd * kXcds; b += gridDim.x) {
-        const uint32_t g = (b % kXcds) * per_xcd + b / kXcds;
-        if (g >= total) continue;
-        uint32_t q, wi;
-        if constexpr (kMode == kWinShared) {
-            const uint32_t h = g / w.group;
-            const uint32_t sw = h / (uint32_t)p.num_jobs;
-            q = h - sw * (uint32_t)p.num_jobs;
-            wi = sw * w.group + (g - h * w.group);
-        } else {
-            q = g / w.nwg;
-            wi = g - q * w.nwg;
-        }
-        const uint32_t v0 = (wi * W + wave) * (V * 64);   // first vector of the window in its slot
+        const uint32_t g = window_of_wave(b, wave, W, per_xcd);
+        if (g >= w.total) continue;
+        uint32_t q = 0, wi = 0;
+        window_at(w, jobs, kMode != kWinShared, g, q, wi);
+        const uint32_t v0 = wi * (V * 64);   // first vector of the window in its slot
         if (v0 >= w.slotv) continue;
         const v4i jb = ((const_job_ptr)p.jobs)[q];
         if (!job_ok(p, jb)) continue;
@@ -314,29 +290,12 @@ constexpr int64_t kMaxGrid = int64_t(1) << 30;
 
 unsigned grid_of(int64_t items) { return (unsigned)(items < kMaxGrid ? items : kMaxGrid); }
 
-// Workgroups of a launch: one per item, at most 2^31 work-items (the rest by the kernels' grid-stride loops).
+// Workgroups of a launch: one per T/64 windows, at most 2^31 work-items (the rest by the kernels' grid-stride loops).
 template <int T>
 unsigned window_grid(uint32_t total) {
-    const uint32_t grid = (total + kXcds - 1) / kXcds * kXcds;
+    const uint32_t grid = window_wgs_per_xcd(total, T / 64) * kXcds;
     constexpr uint32_t cap = (1u << 31) / T;
     return grid < cap ? grid : cap;
-}
-
-// Parameters of a window copy with T * V vectors per workgroup.  False where
-// the window copy does not apply (segment size, or counts beyond 31 bits).
-bool window_params(const CopyParams &p, int64_t wg_vectors, int64_t group, WindowParams &w) {
-    if (p.seg_bytes < kMinWindowSeg || p.seg_bytes > kMaxWindowSeg) return false;
-    const int64_t slotv = p.slot_bytes / 16;
-    const int64_t nwg = ((slotv + wg_vectors - 1) / wg_vectors + group - 1) / group * group;
-    // vector indexes of a window that starts before the slot's end stay below 2^32
-    if (slotv > (int64_t(1) << 30) || nwg * p.num_jobs >= (int64_t(1) << 31) - kXcds) return false;
-    w.segv = (uint32_t)(p.seg_bytes / 16);
-    w.slotv = (uint32_t)slotv;
-    w.nsegs = (uint32_t)(slotv / w.segv);
-    w.magic = (uint32_t)(((uint64_t(1) << 32) + w.segv - 1) / w.segv);
-    w.nwg = (uint32_t)nwg;
-    w.group = (uint32_t)group;
-    return true;
 }
 
 // kRow of a launch with windows of `window` bytes: see copy_window.
@@ -345,12 +304,12 @@ int row_class(const CopyParams &p, int64_t window) {
 }
 
 #define TKV_LAUNCH_WINDOW(T, kernel)                                                                          \
-    hipLaunchKernelGGL((kernel), dim3(window_grid<T>((uint32_t)p.num_jobs * w.nwg)), dim3(T), 0, s, p, w)
+    hipLaunchKernelGGL((kernel), dim3(window_grid<T>(w.total)), dim3(T), 0, s, p, w)
 
 template <int T, bool kRetrieve>
 bool launch_group(const CopyParams &p, hipStream_t s) {
     WindowParams w;
-    if (!window_params(p, T * 16, 1, w)) return false;
+    if (!window_params(p.seg_bytes, p.slot_bytes, p.num_jobs, 16, 0, w)) return false;
     switch (row_class(p, 16 << 10)) {
     case 2: TKV_LAUNCH_WINDOW(T, (group_copy_kernel<T, 2, kRetrieve>)); break;
     case 1: TKV_LAUNCH_WINDOW(T, (group_copy_kernel<T, 1, kRetrieve>)); break;
@@ -361,7 +320,7 @@ bool launch_group(const CopyParams &p, hipStream_t s) {
 
 bool launch_unit(const CopyParams &p, int64_t group, hipStream_t s) {
     WindowParams w;
-    if (!window_params(p, 256 * 4, group, w)) return false;
+    if (!window_params(p.seg_bytes, p.slot_bytes, p.num_jobs, 4, group, w)) return false;
     if (p.seg_bytes % 1024 == 0)
         TKV_LAUNCH_WINDOW(256, (retrieve_unit_kernel<1>));
     else
@@ -372,7 +331,7 @@ bool launch_unit(const CopyParams &p, int64_t group, hipStream_t s) {
 template <int T, int V, WindowMode kMode>
 bool launch_small(const CopyParams &p, int64_t group, hipStream_t s) {
     WindowParams w;
-    if (!window_params(p, T * V, group, w)) return false;
+    if (!window_params(p.seg_bytes, p.slot_bytes, p.num_jobs, V, group, w)) return false;
     if (p.seg_bytes % 1024 == 0)
         TKV_LAUNCH_WINDOW(T, (small_copy_kernel<T, V, kMode, 1>));
     else
@@ -405,9 +364,9 @@ bool launch_stream(const CopyParams &p, hipStream_t s) {
     constexpr double kMiB = 1 << 20;
     if (payload > 1024 * kMiB)
         return kRetrieve && p.seg_bytes < 16384 ? launch_group<256, kRetrieve>(p, s) : launch_group<1024, kRetrieve>(p, s);
-    if (payload > 96 * kMiB || payload <= 24 * kMiB) return launch_small<256, 2, kMode>(p, 1, s);
-    if (payload > 48 * kMiB) return launch_small<512, 16, kMode>(p, 1, s);
-    return launch_small<256, 8, kMode>(p, 1, s);
+    if (payload > 96 * kMiB || payload <= 24 * kMiB) return launch_small<256, 2, kMode>(p, 0, s);
+    if (payload > 48 * kMiB) return launch_small<512, 16, kMode>(p, 0, s);
+    return launch_small<256, 8, kMode>(p, 0, s);
 }
 
 // Whether a device-accessible pointer maps host memory (about 1 us on the host).
@@ -440,9 +399,9 @@ bool in_host_memory(const void *ptr) {
 // groups of 32).
 bool launch_shared(const CopyParams &p, hipStream_t s) {
     const double payload = (double)p.slot_bytes * p.num_jobs;
-    if (payload <= (640 << 20) && p.seg_bytes < 32768) return launch_small<256, 2, kWinShared>(p, 4, s);
-    if (in_host_memory(p.staging)) return launch_unit(p, 1, s);
-    return launch_unit(p, p.seg_bytes * p.nseg > (512 << 10) ? 64 : 32, s);
+    if (payload <= (640 << 20) && p.seg_bytes < 32768) return launch_small<256, 2, kWinShared>(p, 16, s);
+    if (in_host_memory(p.staging)) return launch_unit(p, 4, s);
+    return launch_unit(p, p.seg_bytes * p.nseg > (512 << 10) ? 256 : 128, s);
 }
 
 // Rows of `row_bytes` per segment if the segment is 1, 2, 4, 8 or 16 rows.

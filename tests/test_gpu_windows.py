@@ -18,11 +18,10 @@ SHAPES = {"496": (1, 1, 248, 2), "512": (16, 1, 32, 1), "1040": (13, 1, 40, 2), 
           "512k": (128, 8, 128, 4), "1m": (256, 8, 128, 4)}
 
 
-def _setup(shape, payload, slots_per_job, layout, pad, seed):
+def _setup(shape, payload, slots_per_job, layout, pad, seed, layers=3, nseg=None):
     block, heads, dim, elem = shape
     seg = block * heads * dim * elem
-    nseg = 16 if seg < 131072 else 2
-    layers = 3
+    nseg = nseg or (16 if seg < 131072 else 2)
     slot = 2 * layers * nseg * seg
     n = max(1, payload // slot)
     slots = max(1, int(n * slots_per_job))
@@ -70,9 +69,9 @@ def _expected(pool, staging, bt, jobs, ok, dims, store):
     return pool, staging
 
 
-def _check(shape, payload, op, layout, pad, seed):
+def _check(shape, payload, op, layout, pad, seed, **dims):
     share = {"unit": 0.2, "quad": 0.2}.get(op, 1.0)
-    lo, pool, staging, bt, jobs, ok, dims = _setup(SHAPES[shape], payload, share, layout, pad, seed)
+    lo, pool, staging, bt, jobs, ok, dims = _setup(SHAPES[shape], payload, share, layout, pad, seed, **dims)
     want_pool, want_staging = _expected(pool, staging, bt, jobs, ok, dims, op == "store")
     d_bt, d_jobs = torch.from_numpy(bt).cuda(), torch.from_numpy(jobs).cuda()
     if op == "store":
@@ -99,6 +98,15 @@ def test_segment_sizes(shape, layout, pad, op):
 @pytest.mark.parametrize("mib", [23, 36, 60, 100, 600, 700, 1030])
 def test_launch_shapes(mib, shape, op):
     _check(shape, mib * MIB, op, "kv_first", 16, 11)
+
+
+@pytest.mark.parametrize("op", ["store", "stream", "unit"])
+@pytest.mark.parametrize("shape,layers,nseg", [("512", 1, 1), ("1040", 1, 1), ("1040", 1, 3), ("4k", 1, 1), ("4k", 1, 5),
+                                               ("20k", 1, 1), ("32k", 1, 1), ("64k", 1, 1)])
+@pytest.mark.parametrize("mib", [3, 30, 1100])
+def test_small_slots(mib, shape, layers, nseg, op):
+    # slots below one workgroup's windows or one group, and no multiple of them (thousands of jobs)
+    _check(shape, mib * MIB, op, "block_first", 0, 13, layers=layers, nseg=nseg)
 
 
 @pytest.mark.parametrize("host", [False, True])
