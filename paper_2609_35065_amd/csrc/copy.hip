@@ -24,7 +24,7 @@
 //   each XCD taking one contiguous range of it, non-temporal on both sides.
 //   Large launches move 16 KiB per wave in 1024-lane workgroups; small ones
 //   2 KiB per wave, so that every CU has work and the first store is issued
-//   early (stream_shape below has the sizes and times).
+//   early (stream_shape in window.h has the sizes and times).
 //
 //   Retrieve where jobs share staged chunks: 4 KiB per wave, 256-lane
 //   workgroups, in groups of windows (512 KiB or more); a group of one job is
@@ -298,78 +298,32 @@ unsigned window_grid(uint32_t total) {
     return grid < cap ? grid : cap;
 }
 
-// kRow of a launch with windows of `window` bytes: see copy_window.
-int row_class(const CopyParams &p, int64_t window) {
-    return p.seg_bytes % window == 0 ? 2 : p.seg_bytes % 1024 == 0 ? 1 : 0;
-}
-
 #define TKV_LAUNCH_WINDOW(T, kernel)                                                                          \
     hipLaunchKernelGGL((kernel), dim3(window_grid<T>(w.total)), dim3(T), 0, s, p, w)
 
 template <int T, bool kRetrieve>
-bool launch_group(const CopyParams &p, hipStream_t s) {
-    WindowParams w;
-    if (!window_params(p.seg_bytes, p.slot_bytes, p.num_jobs, 16, 0, w)) return false;
-    switch (row_class(p, 16 << 10)) {
-    case 2: TKV_LAUNCH_WINDOW(T, (group_copy_kernel<T, 2, kRetrieve>)); break;
-    case 1: TKV_LAUNCH_WINDOW(T, (group_copy_kernel<T, 1, kRetrieve>)); break;
-    default: TKV_LAUNCH_WINDOW(T, (group_copy_kernel<T, 0, kRetrieve>)); break;
+void launch_group(const CopyParams &p, const WindowParams &w, hipStream_t s) {
+    if constexpr (T == 1024) {   // (256-lane workgroups run segments below 16 KiB)
+        if (p.seg_bytes % (16 << 10) == 0) {
+            TKV_LAUNCH_WINDOW(T, (group_copy_kernel<T, 2, kRetrieve>));
+            return;
+        }
     }
-    return true;
-}
-
-bool launch_unit(const CopyParams &p, int64_t group, hipStream_t s) {
-    WindowParams w;
-    if (!window_params(p.seg_bytes, p.slot_bytes, p.num_jobs, 4, group, w)) return false;
     if (p.seg_bytes % 1024 == 0)
-        TKV_LAUNCH_WINDOW(256, (retrieve_unit_kernel<1>));
+        TKV_LAUNCH_WINDOW(T, (group_copy_kernel<T, 1, kRetrieve>));
     else
-        TKV_LAUNCH_WINDOW(256, (retrieve_unit_kernel<0>));
-    return true;
+        TKV_LAUNCH_WINDOW(T, (group_copy_kernel<T, 0, kRetrieve>));
 }
 
 template <int T, int V, WindowMode kMode>
-bool launch_small(const CopyParams &p, int64_t group, hipStream_t s) {
-    WindowParams w;
-    if (!window_params(p.seg_bytes, p.slot_bytes, p.num_jobs, V, group, w)) return false;
+void launch_small(const CopyParams &p, const WindowParams &w, hipStream_t s) {
     if (p.seg_bytes % 1024 == 0)
         TKV_LAUNCH_WINDOW(T, (small_copy_kernel<T, V, kMode, 1>));
     else
         TKV_LAUNCH_WINDOW(T, (small_copy_kernel<T, V, kMode, 0>));
-    return true;
 }
 
-#undef TKV_LAUNCH_WINDOW
-
-// Store and streaming retrieve, by payload.  Median us over rotating buffers,
-// 32 KiB segments unless noted, store / retrieve:
-//   payload      2 KiB a wave    8 KiB          16 KiB, T=512   16 KiB, T=1024
-//   8 MiB (4K)     6.0 /   5.8    8.1 /   6.4    12.2 /  11.3     13.6 /  14.0
-//   32 MiB        14.7 /  14.3   13.3 /  13.6    16.9 /  14.7     18.4 /  17.5
-//   96 MiB        36.7 /  37.0   37.7 /  40.9    33.4 /  35.0     41.9 /  42.6
-//   128 MiB       49.4 /  46.7   54.8 /  55.5    53.4 /  57.6     48.6 /  53.1
-//   512 MiB        182 /   183    203 /   207     199 /   209      197 /   204
-//   8 GiB         2968 /  3147      -            2912 /  3164     2889 /  3131
-//   8 GiB (64K)   2780 /  2875      -            2791 /  2754     2743 /  2695
-// A CU holds 24 waves of the 16 KiB shape and 32 of the 8 KiB one: payloads up
-// to 96 MiB and up to 48 MiB run as one full set of resident waves, which beats
-// many short ones; otherwise short waves win until the launch is long enough
-// for its start and end not to matter.  (A large streaming retrieve of segments
-// below 16 KiB runs 256-lane workgroups: 796 against 792 us with 1024 lanes at
-// 2 GiB of 4 KiB segments; the store keeps 1024: 738 against 745 us.)
-template <bool kRetrieve>
-bool launch_stream(const CopyParams &p, hipStream_t s) {
-    constexpr WindowMode kMode = kRetrieve ? kWinStream : kWinStore;
-    const double payload = (double)p.slot_bytes * p.num_jobs;
-    constexpr double kMiB = 1 << 20;
-    if (payload > 1024 * kMiB)
-        return kRetrieve && p.seg_bytes < 16384 ? launch_group<256, kRetrieve>(p, s) : launch_group<1024, kRetrieve>(p, s);
-    if (payload > 96 * kMiB || payload <= 24 * kMiB) return launch_small<256, 2, kMode>(p, 0, s);
-    if (payload > 48 * kMiB) return launch_small<512, 16, kMode>(p, 0, s);
-    return launch_small<256, 8, kMode>(p, 0, s);
-}
-
-// Whether a device-accessible pointer maps host memory (about 1 us on the host).
+// Whether a device-accessible pointer maps host memory (0.24 us on the host).
 bool in_host_memory(const void *ptr) {
     hipPointerAttribute_t at;
     if (hipPointerGetAttributes(&at, ptr) != hipSuccess) {
@@ -379,30 +333,46 @@ bool in_host_memory(const void *ptr) {
     return at.type == hipMemoryTypeHost;
 }
 
-// Retrieve with shared chunks.  Groups of one plane's bytes (at least 512 KiB
-// = 32 workgroups): median ms by workgroups a group, 4 KiB a wave, 8 requests
-// per chunk:
-//   segment   1      8      32     64    (before)
-//   4 KiB    1.08   0.98   0.93   0.94    0.99
-//   16 KiB   2.11   1.95   1.58   1.59    2.29
-//   20 KiB   1.68   1.67   1.60   1.60    2.07   (ragged sharing)
-//   32 KiB   3.90   3.81   3.12   3.10    3.16
-//   64 KiB   4.65   3.82   3.77   3.46    3.62
-// Below, the pieces of a block are written far apart in time; 2 KiB and 8 KiB
-// a wave are 5-40 % slower at these sizes.  A launch that writes up to 640 MiB
-// in segments below 32 KiB is the exception: it lives in the caches, and 2 KiB
-// a wave in groups of 4 is faster (512 MiB of 4 KiB segments: 90 against 104
-// us; 640 MiB of 20 KiB ones: 114 against 129 us).
-// Staged chunks in host memory are read through the link, where what counts is
-// that the jobs sharing a chunk read the same bytes at the same time: groups of
-// one (1,024 requests on 48 chunks: 29.3 ms; 31.0 in groups of 8, 33.5 in
-// groups of 32).
-bool launch_shared(const CopyParams &p, hipStream_t s) {
-    const double payload = (double)p.slot_bytes * p.num_jobs;
-    if (payload <= (640 << 20) && p.seg_bytes < 32768) return launch_small<256, 2, kWinShared>(p, 16, s);
-    if (in_host_memory(p.staging)) return launch_unit(p, 4, s);
-    return launch_unit(p, p.seg_bytes * p.nseg > (512 << 10) ? 256 : 128, s);
+double payload_of(const CopyParams &p) { return (double)p.slot_bytes * p.num_jobs; }
+
+template <bool kRetrieve>
+bool launch_stream_shape(const CopyParams &p, const CopyShape &c, hipStream_t s) {
+    constexpr WindowMode kMode = kRetrieve ? kWinStream : kWinStore;
+    WindowParams w;
+    if (!window_params(p.seg_bytes, p.slot_bytes, p.num_jobs, c.vectors, c.group, w)) return false;
+    if (c.vectors == 2) launch_small<256, 2, kMode>(p, w, s);
+    else if (c.vectors == 8) launch_small<256, 8, kMode>(p, w, s);
+    else if (c.threads == 512) launch_small<512, 16, kMode>(p, w, s);
+    else if (kRetrieve && c.threads == 256) launch_group<256, true>(p, w, s);
+    else launch_group<1024, kRetrieve>(p, w, s);
+    return true;
 }
+
+template <bool kRetrieve>
+bool launch_stream(const CopyParams &p, hipStream_t s) {
+    const double payload = payload_of(p);
+    const bool host = stream_asks_host(kRetrieve, payload) && in_host_memory(p.staging);
+    return launch_stream_shape<kRetrieve>(p, stream_shape(kRetrieve, payload, p.seg_bytes, host), s);
+}
+
+bool launch_shared(const CopyParams &p, hipStream_t s) {
+    const double payload = payload_of(p);
+    const bool host = (p.num_jobs == 1 || !shared_small(payload, p.seg_bytes)) && in_host_memory(p.staging);
+    if (host && p.num_jobs == 1)
+        return launch_stream_shape<true>(p, stream_shape(true, payload, p.seg_bytes, true), s);
+    const CopyShape c = shared_shape(payload, p.seg_bytes, p.seg_bytes * p.nseg, host);
+    WindowParams w;
+    if (!window_params(p.seg_bytes, p.slot_bytes, p.num_jobs, c.vectors, c.group, w)) return false;
+    if (c.vectors == 2)
+        launch_small<256, 2, kWinShared>(p, w, s);
+    else if (p.seg_bytes % 1024 == 0)
+        TKV_LAUNCH_WINDOW(256, (retrieve_unit_kernel<1>));
+    else
+        TKV_LAUNCH_WINDOW(256, (retrieve_unit_kernel<0>));
+    return true;
+}
+
+#undef TKV_LAUNCH_WINDOW
 
 // Rows of `row_bytes` per segment if the segment is 1, 2, 4, 8 or 16 rows.
 int rows_of(int64_t seg_bytes, int64_t row_bytes) {

@@ -73,4 +73,84 @@ constexpr void window_at(const WindowParams &w, uint32_t jobs, bool one_group, u
     }
 }
 
+// ---------------------------------------------------------------------------
+// Launch shapes: lanes a workgroup, vectors a lane (KiB a window) and windows a
+// group (0: a job's windows are one group), from the launch's payload in bytes.
+// ---------------------------------------------------------------------------
+struct CopyShape {
+    int threads, vectors, group;
+};
+
+constexpr double kMiB = 1 << 20;
+
+// Store and streaming retrieve.  Median us over rotating buffers, 32 KiB
+// segments unless noted, store / retrieve:
+//   payload      2 KiB a wave    8 KiB          16 KiB, T=512   16 KiB, T=1024
+//   8 MiB (4K)     6.0 /   5.8    8.1 /   6.4    12.2 /  11.3     13.6 /  14.0
+//   32 MiB        14.7 /  14.3   13.3 /  13.6    16.9 /  14.7     18.4 /  17.5
+//   96 MiB        36.7 /  37.0   37.7 /  40.9    33.4 /  35.0     41.9 /  42.6
+//   128 MiB       49.4 /  46.7   54.8 /  55.5    53.4 /  57.6     48.6 /  53.1
+//   512 MiB        182 /   183    203 /   207     199 /   209      197 /   204
+//   8 GiB         2968 /  3147      -            2912 /  3164     2889 /  3131
+//   8 GiB (64K)   2780 /  2875      -            2791 /  2754     2743 /  2695
+// The edges (24, 48 and 96 MiB) are those of the table.  A CU holds 24 waves of
+// the 16 KiB shape, so 96 MiB is one full set of them; above it short waves win
+// until the launch is long enough for its start and end not to matter.  (A
+// large streaming retrieve of segments below 16 KiB runs 256-lane workgroups:
+// 796 against 792 us with 1024 lanes at 2 GiB of 4 KiB segments; the store
+// keeps 1024: 738 against 745 us.)
+//
+// With the staged chunks in host memory the link sets the time.  Up to 96 MiB
+// it wants reads that are issued early and together, 16 KiB a wave, and writes
+// in short waves (us at 32 KiB segments, retrieve / store):
+//   payload      2 KiB a wave    8 KiB          16 KiB, T=512   16 KiB, T=1024
+//   16 MiB         324 /   338    333 /   354     314 /   364      306 /   364
+//   36 MiB         696 /   728    734 /   738     703 /   764      700 /   782
+//   60 MiB        1152 /  1184   1177 /  1189    1168 /  1243     1170 /  1258
+// and above the shapes differ by 1 %.
+constexpr bool stream_asks_host(bool retrieve, double payload) {
+    return payload <= 96 * kMiB && (retrieve || payload > 24 * kMiB);
+}
+
+constexpr CopyShape stream_shape(bool retrieve, double payload, int64_t seg_bytes, bool host) {
+    if (host && payload <= 96 * kMiB)
+        return retrieve && payload <= 48 * kMiB ? CopyShape{1024, 16, 0} : CopyShape{256, 2, 0};
+    if (payload > 1024 * kMiB) return {retrieve && seg_bytes < 16384 ? 256 : 1024, 16, 0};
+    if (payload > 96 * kMiB || payload <= 24 * kMiB) return {256, 2, 0};
+    if (payload > 48 * kMiB) return {512, 16, 0};
+    return {256, 8, 0};
+}
+
+// Retrieve with shared chunks.  Groups of 512 KiB, or of 1 MiB where a plane's
+// segments are more than 512 KiB: median ms by KiB a group, 4 KiB a wave, 8
+// requests per chunk:
+//   segment    16    128    512   1024
+//   4 KiB    1.08   0.98   0.93   0.94
+//   16 KiB   2.11   1.95   1.58   1.59
+//   20 KiB   1.68   1.67   1.60   1.60   (ragged sharing)
+//   32 KiB   3.90   3.81   3.12   3.10
+//   64 KiB   4.65   3.82   3.77   3.46
+// Below, the pieces of a block are written far apart in time; 2 KiB and 8 KiB
+// a wave are 5-40 % slower at these sizes.  A launch that writes up to 640 MiB
+// in segments below 32 KiB is the exception: it lives in the caches, and 2 KiB
+// a wave in groups of 32 KiB is faster (512 MiB of 4 KiB segments: 90 against
+// 104 us; 640 MiB of 20 KiB ones: 114 against 129 us).
+//
+// Staged chunks in host memory are read through the link, where what counts is
+// that the jobs sharing a chunk read the same bytes at the same time: groups of
+// 8 KiB, 2 KiB a wave (3,072 jobs on 48 chunks of 16 MiB: 14.1 ms, 16.6 in
+// groups of 64 KiB and 17.9 of 256 KiB; 400 MiB and less: 0-10 % faster than
+// 4 KiB a wave in groups of 16 KiB).  The exception above needs no such rule:
+// groups of 32 KiB measured as fast there.  A single job shares nothing and
+// takes the streaming shape (8 MiB: 158 us; 191 in groups).
+constexpr bool shared_small(double payload, int64_t seg_bytes) {
+    return payload <= 640 * kMiB && seg_bytes < 32768;
+}
+
+constexpr CopyShape shared_shape(double payload, int64_t seg_bytes, int64_t plane_bytes, bool host) {
+    if (shared_small(payload, seg_bytes)) return {256, 2, 16};
+    if (host) return {256, 2, 4};
+    return {256, 4, plane_bytes > (512 << 10) ? 256 : 128};
+}
+
 }  // namespace tkv

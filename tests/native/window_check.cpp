@@ -67,6 +67,23 @@ int main() {
     CHECK(!tkv::window_params(1 << 16, (int64_t(1) << 34) + (1 << 17), 1, 4, 128, w));
     CHECK(tkv::window_params(1024, 2048, 0x7fffff00, 2, 16, w) && w.total == 0x7fffff00u);
     CHECK(!tkv::window_params(1024, 2048, 0x7fffff01, 2, 16, w));
+    // launch shapes: with the chunks in host memory a retrieve of up to 48 MiB reads 16 KiB a wave, other small
+    // copies move 2 KiB a wave, and jobs that share a chunk are at most 8 KiB apart (32 KiB in small launches of
+    // small segments); the question is asked wherever the answer matters
+    for (double mib = 0.5; mib < 4096; mib *= 1.1)
+        for (int64_t seg : {1024, 20480, 32768, 65536})
+            for (int retrieve = 0; retrieve < 2; ++retrieve) {
+                const double bytes = mib * tkv::kMiB;
+                const tkv::CopyShape d = tkv::stream_shape(retrieve, bytes, seg, false);
+                const tkv::CopyShape h = tkv::stream_shape(retrieve, bytes, seg, true);
+                if (mib <= 96) CHECK(h.vectors == (retrieve && mib <= 48 ? 16 : 2));
+                if (!tkv::stream_asks_host(retrieve, bytes)) CHECK(d.threads == h.threads && d.vectors == h.vectors);
+                const tkv::CopyShape sh = tkv::shared_shape(bytes, seg, 16 * seg, true);
+                const tkv::CopyShape sd = tkv::shared_shape(bytes, seg, 16 * seg, false);
+                CHECK(sh.vectors * sh.group <= (tkv::shared_small(bytes, seg) ? 32 : 8));
+                if (tkv::shared_small(bytes, seg)) CHECK(sh.vectors == sd.vectors && sh.group == sd.group);
+                CHECK(d.group == 0 && h.group == 0 && sd.group > 0 && sh.group > 0);
+            }
     puts("window check ok");
     return 0;
 }

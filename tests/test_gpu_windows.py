@@ -69,16 +69,21 @@ def _expected(pool, staging, bt, jobs, ok, dims, store):
     return pool, staging
 
 
-def _check(shape, payload, op, layout, pad, seed, **dims):
+def _check(shape, payload, op, layout, pad, seed, host=False, **dims):
     share = {"unit": 0.2, "quad": 0.2}.get(op, 1.0)
     lo, pool, staging, bt, jobs, ok, dims = _setup(SHAPES[shape], payload, share, layout, pad, seed, **dims)
     want_pool, want_staging = _expected(pool, staging, bt, jobs, ok, dims, op == "store")
     d_bt, d_jobs = torch.from_numpy(bt).cuda(), torch.from_numpy(jobs).cuda()
+    at = staging
+    if host:
+        staging = torch.empty(staging.numel(), dtype=torch.int64, pin_memory=True).copy_(staging)
+        want_staging = want_staging.cpu()
+        at = kv.kv_host_device_pointer(staging.data_ptr())
     if op == "store":
-        kv.kv_store_gather(lo, staging, pool, d_bt, bt.shape[1], bt.shape[0], d_jobs, len(jobs))
+        kv.kv_store_gather(lo, at, pool, d_bt, bt.shape[1], bt.shape[0], d_jobs, len(jobs))
     else:
         kind = {"unit": kv.KV_RETRIEVE_UNIT, "stream": kv.KV_RETRIEVE_STREAM, "quad": kv.KV_RETRIEVE_QUAD}[op]
-        kv.kv_retrieve_scatter_as(kind, lo, staging, pool, d_bt, bt.shape[1], bt.shape[0], d_jobs, len(jobs))
+        kv.kv_retrieve_scatter_as(kind, lo, at, pool, d_bt, bt.shape[1], bt.shape[0], d_jobs, len(jobs))
     torch.cuda.synchronize()
     assert torch.equal(staging, want_staging)
     for a, b in zip(pool, want_pool):
@@ -107,6 +112,14 @@ def test_launch_shapes(mib, shape, op):
 def test_small_slots(mib, shape, layers, nseg, op):
     # slots below one workgroup's windows or one group, and no multiple of them (thousands of jobs)
     _check(shape, mib * MIB, op, "block_first", 0, 13, layers=layers, nseg=nseg)
+
+
+@pytest.mark.parametrize("op", ["store", "stream", "unit"])
+@pytest.mark.parametrize("shape", ["512", "1040", "4k", "20k", "32k", "64k"])
+@pytest.mark.parametrize("mib", [1, 20, 60])
+def test_host_memory(mib, shape, op):
+    # staged chunks in host memory: one job, and payloads on both sides of the sizes at which the shape changes
+    _check(shape, mib * MIB, op, "kv_first", 0, 17, host=True)
 
 
 @pytest.mark.parametrize("host", [False, True])
