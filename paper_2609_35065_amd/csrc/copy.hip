@@ -340,7 +340,9 @@ bool launch_stream_shape(const CopyParams &p, const CopyShape &c, hipStream_t s)
     constexpr WindowMode kMode = kRetrieve ? kWinStream : kWinStore;
     WindowParams w;
     if (!window_params(p.seg_bytes, p.slot_bytes, p.num_jobs, c.vectors, c.group, w)) return false;
-    if (c.vectors == 2) launch_small<256, 2, kMode>(p, w, s);
+    if (kRetrieve && c.cached && c.vectors == 2) launch_small<256, 2, kWinShared>(p, w, s);
+    else if (kRetrieve && c.cached) launch_small<256, 8, kWinShared>(p, w, s);
+    else if (c.vectors == 2) launch_small<256, 2, kMode>(p, w, s);
     else if (c.vectors == 8) launch_small<256, 8, kMode>(p, w, s);
     else if (c.threads == 512) launch_small<512, 16, kMode>(p, w, s);
     else if (kRetrieve && c.threads == 256) launch_group<256, true>(p, w, s);

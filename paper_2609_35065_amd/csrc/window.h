@@ -76,9 +76,11 @@ constexpr void window_at(const WindowParams &w, uint32_t jobs, bool one_group, u
 // ---------------------------------------------------------------------------
 // Launch shapes: lanes a workgroup, vectors a lane (KiB a window) and windows a
 // group (0: a job's windows are one group), from the launch's payload in bytes.
+// cached: a streaming retrieve that reads through the caches.
 // ---------------------------------------------------------------------------
 struct CopyShape {
     int threads, vectors, group;
+    bool cached = false;
 };
 
 constexpr double kMiB = 1 << 20;
@@ -108,6 +110,27 @@ constexpr double kMiB = 1 << 20;
 //   36 MiB         696 /   728    734 /   738     703 /   764      700 /   782
 //   60 MiB        1152 /  1184   1177 /  1189    1168 /  1243     1170 /  1258
 // and above the shapes differ by 1 %.
+//
+// Non-temporal loads suit chunks that come from HBM; chunks that were just
+// staged or stored may still lie in the 256 MiB memory-side cache, and cached
+// loads read them faster (us, cached / non-temporal; cached 8 KiB a wave up to
+// 48 MiB, then 2 KiB):
+//   segments, payload        from HBM        from the cache
+//   20 KiB,  40 MiB        19.2 / 18.4       16.0 / 17.4
+//   20 KiB,  60 MiB        27.1 / 26.0       18.9 / 25.7
+//   20 KiB, 130 MiB        56.0 / 54.8       35.2 / 54.3
+//   32 KiB,  60 MiB        27.3 / 25.8       18.5 / 23.0
+//   32 KiB,  90 MiB        38.1 / 35.7       25.0 / 32.0
+// Segments of 4 KiB x 2^n (up to 256 KiB) take the non-temporal side of that
+// trade, 5-7 % from HBM, where a reused chunk comes from in ordinary use; for
+// other sizes that side is worth at most 8 % from HBM, mostly under 3 %, and
+// costs up to 1.7 times from the cache (7,936-byte segments), so they take the
+// cached side.
+constexpr bool stream_cached(double payload, int64_t seg_bytes) {
+    const bool pow2 = seg_bytes >= 4096 && seg_bytes <= (256 << 10) && (seg_bytes & (seg_bytes - 1)) == 0;
+    return !pow2 && payload > 24 * kMiB && payload <= 256 * kMiB;
+}
+
 constexpr bool stream_asks_host(bool retrieve, double payload) {
     return payload <= 96 * kMiB && (retrieve || payload > 24 * kMiB);
 }
@@ -115,6 +138,7 @@ constexpr bool stream_asks_host(bool retrieve, double payload) {
 constexpr CopyShape stream_shape(bool retrieve, double payload, int64_t seg_bytes, bool host) {
     if (host && payload <= 96 * kMiB)
         return retrieve && payload <= 48 * kMiB ? CopyShape{1024, 16, 0} : CopyShape{256, 2, 0};
+    if (retrieve && stream_cached(payload, seg_bytes)) return {256, payload > 48 * kMiB ? 2 : 8, 0, true};
     if (payload > 1024 * kMiB) return {retrieve && seg_bytes < 16384 ? 256 : 1024, 16, 0};
     if (payload > 96 * kMiB || payload <= 24 * kMiB) return {256, 2, 0};
     if (payload > 48 * kMiB) return {512, 16, 0};

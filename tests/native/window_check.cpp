@@ -82,6 +82,9 @@ int main() {
                 const tkv::CopyShape sd = tkv::shared_shape(bytes, seg, 16 * seg, false);
                 CHECK(sh.vectors * sh.group <= (tkv::shared_small(bytes, seg) ? 32 : 8));
                 if (tkv::shared_small(bytes, seg)) CHECK(sh.vectors == sd.vectors && sh.group == sd.group);
+                // cached loads: from 24 to 256 MiB of segments that are not 4 KiB x 2^n
+                CHECK(d.cached == (retrieve && (seg == 1024 || seg == 20480) && mib > 24 && mib <= 256));
+                CHECK((!d.cached || d.vectors == (mib > 48 ? 2 : 8)) && !(h.cached && mib <= 96));
                 CHECK(d.group == 0 && h.group == 0 && sd.group > 0 && sh.group > 0);
             }
     puts("window check ok");
