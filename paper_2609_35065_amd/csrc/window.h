@@ -145,9 +145,9 @@ constexpr CopyShape stream_shape(bool retrieve, double payload, int64_t seg_byte
     return {256, 8, 0};
 }
 
-// Retrieve with shared chunks.  Groups of 512 KiB, or of 1 MiB where a plane's
-// segments are more than 512 KiB: median ms by KiB a group, 4 KiB a wave, 8
-// requests per chunk:
+// Retrieve with shared chunks.  Large launches: groups of 512 KiB, or of 1 MiB
+// where a plane's segments are more than 512 KiB: median ms by KiB a group, 4 KiB
+// a wave, 8 requests per chunk:
 //   segment    16    128    512   1024
 //   4 KiB    1.08   0.98   0.93   0.94
 //   16 KiB   2.11   1.95   1.58   1.59
@@ -155,10 +155,30 @@ constexpr CopyShape stream_shape(bool retrieve, double payload, int64_t seg_byte
 //   32 KiB   3.90   3.81   3.12   3.10
 //   64 KiB   4.65   3.82   3.77   3.46
 // Below, the pieces of a block are written far apart in time; 2 KiB and 8 KiB
-// a wave are 5-40 % slower at these sizes.  A launch that writes up to 640 MiB
-// in segments below 32 KiB is the exception: it lives in the caches, and 2 KiB
-// a wave in groups of 32 KiB is faster (512 MiB of 4 KiB segments: 90 against
-// 104 us; 640 MiB of 20 KiB ones: 114 against 129 us).
+// a wave are 5-40 % slower at these sizes.  Segments below 32 KiB with planes of
+// 128 KiB to 512 KiB take groups of a plane, 256 KiB at least: within 1 % on
+// lists grouped by slot and up to 1.5 times as fast on lists that are not, where
+// a group is read again only after the same group of every other chunk (us by
+// KiB a group, 8 requests per chunk):
+//                     grouped: 64   128   256   512   not grouped: 64   128   256   512
+//   8 KiB,  3 GiB             803   695   674   676               682   762   762   768
+//   8 KiB,  6 GiB            1586  1382  1349  1339              1508  1540  1572  2395
+//   16 KiB, 3 GiB             894   751   672   663               680   673   892  1149
+// Smaller planes keep 512 KiB: 4 KiB segments, 6 GiB, 1.31 ms grouped against
+// 1.37 in groups of 256 KiB, 2.36 against 2.32 not grouped.
+//
+// Launches of up to 1 GiB in segments below 32 KiB live in the caches.  Up to
+// 512 MiB 2 KiB a wave in groups of 32 KiB is the fastest (500 MiB of 4 KiB
+// segments, 8 requests per chunk: 90 us; 98 with 4 KiB a wave in groups of 64
+// KiB, 103 in groups of 512 KiB), from there to 1 GiB 4 KiB a wave in groups of
+// 64 KiB (us by requests per chunk, and 8 on a list that is not grouped):
+//                                  1     2     8   not grouped
+//   700 MiB of 4 KiB,  64 KiB    277   205   134   135
+//                     512 KiB    281   208   144   162
+//   600 MiB of 4 KiB,  64 KiB    238   170   117   117
+//                      32 KiB    238   183   111   117
+//   600 MiB of 16 KiB, 64 KiB    237   168   119   118
+//                      32 KiB    236   193   110   115
 //
 // Staged chunks in host memory are read through the link, where what counts is
 // that the jobs sharing a chunk read the same bytes at the same time: groups of
@@ -168,12 +188,17 @@ constexpr CopyShape stream_shape(bool retrieve, double payload, int64_t seg_byte
 // groups of 32 KiB measured as fast there.  A single job shares nothing and
 // takes the streaming shape (8 MiB: 158 us; 191 in groups).
 constexpr bool shared_small(double payload, int64_t seg_bytes) {
-    return payload <= 640 * kMiB && seg_bytes < 32768;
+    return payload <= 512 * kMiB && seg_bytes < 32768;
 }
 
 constexpr CopyShape shared_shape(double payload, int64_t seg_bytes, int64_t plane_bytes, bool host) {
     if (shared_small(payload, seg_bytes)) return {256, 2, 16};
     if (host) return {256, 2, 4};
+    if (seg_bytes < 32768) {
+        if (payload <= 1024 * kMiB) return {256, 4, 16};
+        if (plane_bytes >= (128 << 10) && plane_bytes <= (512 << 10))
+            return {256, 4, plane_bytes < (256 << 10) ? 64 : (int)((plane_bytes + 4095) / 4096)};
+    }
     return {256, 4, plane_bytes > (512 << 10) ? 256 : 128};
 }
 

@@ -85,8 +85,15 @@ int main() {
                 // cached loads: from 24 to 256 MiB of segments that are not 4 KiB x 2^n
                 CHECK(d.cached == (retrieve && (seg == 1024 || seg == 20480) && mib > 24 && mib <= 256));
                 CHECK((!d.cached || d.vectors == (mib > 48 ? 2 : 8)) && !(h.cached && mib <= 96));
+                // groups (4 KiB a wave): 64 KiB up to 1 GiB of small segments, then no more than a plane, unless
+                // it is smaller than 128 KiB
+                if (seg < 32768 && !tkv::shared_small(bytes, seg))
+                    CHECK(sd.vectors == 4 && sd.group == (mib <= 1024 ? 16 : seg == 20480 ? 80 : 128));
+                if (seg >= 32768) CHECK(sd.vectors == 4 && sd.group == (seg == 32768 ? 128 : 256));
                 CHECK(d.group == 0 && h.group == 0 && sd.group > 0 && sh.group > 0);
             }
+    CHECK(tkv::shared_shape(3e9, 8192, 128 << 10, false).group == 64);
+    CHECK(tkv::shared_shape(3e9, 16384, 256 << 10, false).group == 64);
     puts("window check ok");
     return 0;
 }
