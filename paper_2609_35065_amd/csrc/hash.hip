@@ -56,13 +56,13 @@ __device__ __forceinline__ uint32_t writelane(uint32_t old, uint32_t val) {
 // every lane number is an immediate.  The eight digests are read into scalar
 // registers before the eight dependent steps, keeping v_readlane latency off
 // the chain.  kAll: lane K+j takes hash K+j; otherwise lane K/8 takes the hash
-// before step K.  The last group of a request has `left` blocks; up to seven
-// steps past them run on whatever the tile holds there and are not stored (62
-// blocks: 5.1 us; 7.3 us as a loop of single steps with lane numbers in registers).
+// before step K.  The last group of a request runs its `left` blocks, a multiple
+// of eight (62 blocks, 56 of them here: 5.8 us a launch, 7.3 as a loop of single
+// steps).
 template <bool kAll, int K>
 struct ChainGroup {
     static __device__ __forceinline__ void run(uint64_t &h, uint64_t d, uint32_t &lo, uint32_t &hi, int left) {
-        if (kAll && K > 0 && K >= left) return;
+        if (kAll && K >= left) return;
         uint64_t dk[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) dk[j] = readlane64(d, K + j);
@@ -113,7 +113,12 @@ __device__ __forceinline__ uint64_t block_digest(const int32_t *tp) {
 // the scalar ALU: for each group of 64 blocks, lane k holds digest k and
 // v_readlane moves it to scalar registers.  In the last tile v_writelane parks
 // h_k in lane k, which then stores the group's 64 hashes in one write, so that
-// nothing is left to do when the chain ends.
+// nothing is left to do when the chain ends.  The last one to seven blocks run
+// as single steps: where requests are many and short, workgroups wait for their
+// turn on a CU and every step counts (100,000 requests of one block 91 us, 130
+// with eight steps for it; 20,000 of nine 27 against 35).  All waves have the
+// same priority: raised for the chain it holds up the digests that the other
+// chains on the CU wait for (2,000 requests of 512 blocks 50 us, 61 with it).
 __global__ __launch_bounds__(kHashThreads) void hash_kernel(const int32_t *__restrict__ tokens,
                                                            const int64_t *__restrict__ tok_off, uint64_t seed,
                                                            const int64_t *__restrict__ blk_off,
@@ -135,7 +140,6 @@ __global__ __launch_bounds__(kHashThreads) void hash_kernel(const int32_t *__res
 
     if (tid < nb) dig[0][tid] = block_digest(tk + (int64_t)tid * 16);
     __syncthreads();
-    if (wave == 0) __builtin_amdgcn_s_setprio(3);   // the chain issues before the waves that share its SIMD
     uint64_t h = seed;   // live in wave 0 only
     int cur = 0;         // t mod 3
     for (int64_t t = 0; t < ntiles; ++t) {
@@ -152,8 +156,17 @@ __global__ __launch_bounds__(kHashThreads) void hash_kernel(const int32_t *__res
             } else {
                 const int left = (int)(nb - tb);
                 for (int g = 0; g < left; g += kWave) {
+                    const uint64_t d = dt[g + lane];
+                    const int cnt = left - g < kWave ? left - g : kWave;
                     uint32_t mine_lo = 0, mine_hi = 0;
-                    ChainGroup<true, 0>::run(h, dt[g + lane], mine_lo, mine_hi, left - g);
+                    ChainGroup<true, 0>::run(h, d, mine_lo, mine_hi, cnt & ~7);
+                    for (int k = cnt & ~7; k < cnt; ++k) {
+                        h = mix64(h ^ readlane64(d, k));
+                        if (lane == k) {
+                            mine_lo = (uint32_t)h;
+                            mine_hi = (uint32_t)(h >> 32);
+                        }
+                    }
                     if (g + lane < left) out[o0 + tb + g + lane] = ((uint64_t)mine_hi << 32) | mine_lo;
                 }
             }
@@ -173,6 +186,7 @@ __global__ __launch_bounds__(kHashThreads) void hash_kernel(const int32_t *__res
                 }
             }
         }
+        if (t + 1 == ntiles) break;   // nothing reads the tiles any more
         __syncthreads();
         cur = next;
     }

@@ -34,3 +34,8 @@ def test_one_request(blocks):
 
 def test_batch():
     _run([b * 16 for b in BLOCKS] * 40, 2 ** 64 - 1)
+
+
+def test_short_requests():
+    # every length from nothing to past a group of 64, whose last blocks run as single steps, some tokens over
+    _run([b * 16 + b % 16 for b in range(0, 75)] * 8, 3)
