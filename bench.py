@@ -82,20 +82,27 @@ def _load_traffic(kernel: str, workload: str, variant: str = None):
 # Kernel symbols, and the summaries of rocprofv3 output committed under profiles/
 # ---------------------------------------------------------------------------
 
-def _symbol(kind: str, w) -> str:
-    """The __global__ function (copy.hip) a large copy launch of this kind runs for the workload's segment size
-    (store and stream: more than 1 GiB of payload; unit and pair: more than 640 MiB, or segments of 32 KiB and
-    up).  Smaller launches run small_copy_kernel, segments outside 512 bytes .. 512 KiB copy_generic_kernel."""
-    seg = w.shape.seg_bytes
+# Segments that the window copies take (kMinWindowSeg and kMaxWindowSeg of window.h); others run the generic copy.
+WINDOW_SEGMENTS = (512, 512 << 10)
+
+
+def _copy_symbol(kind: str, seg: int) -> str:
+    """The __global__ function (copy.hip) a large copy launch of this kind runs for segments of this size (store and
+    stream: more than 1 GiB of payload; unit and pair: more than 512 MiB, or segments of 32 KiB and up).  Smaller
+    launches run small_copy_kernel, segments outside 512 bytes .. 512 KiB copy_generic_kernel."""
     if kind == "quad" and seg in (4096, 8192, 16384, 32768, 65536):
         return f"retrieve_quad_kernel<{seg // 4096}>"
     retrieve = kind != "store"
-    if not 512 <= seg <= 512 << 10:
+    if not WINDOW_SEGMENTS[0] <= seg <= WINDOW_SEGMENTS[1]:
         return f"copy_generic_kernel<{'true' if retrieve else 'false'}>"
     if kind in ("unit", "pair", "quad"):
         return f"retrieve_unit_kernel<{1 if seg % 1024 == 0 else 0}>"
     row = 2 if seg % 16384 == 0 else 1 if seg % 1024 == 0 else 0
     return f"group_copy_kernel<{256 if retrieve and seg < 16384 else 1024}, {row}, {'true' if retrieve else 'false'}>"
+
+
+def _symbol(kind: str, w) -> str:
+    return _copy_symbol(kind, w.shape.seg_bytes)
 
 
 def _label(symbol: str) -> str:
@@ -216,9 +223,10 @@ def _counter_medians(directory: str):
 
 def _calibration_scales(cal_dir: str):
     """FETCH_SIZE and WRITE_SIZE scale factors from the calibration copy (4 GiB each way)."""
-    w_cal = 4 << 30
-    cf = [v for (k, c), v in _counter_medians(os.path.join(cal_dir, "cal_fetch")).items() if "copy_generic" in k]
-    cw = [v for (k, c), v in _counter_medians(os.path.join(cal_dir, "cal_write")).items() if "copy_generic" in k]
+    w_cal = CALIBRATION_SLOTS * 2 * CALIBRATION_SEG
+    sym = _copy_symbol("unit", CALIBRATION_SEG)
+    cf = [v for (k, c), v in _counter_medians(os.path.join(cal_dir, "cal_fetch")).items() if k == sym]
+    cw = [v for (k, c), v in _counter_medians(os.path.join(cal_dir, "cal_write")).items() if k == sym]
     return w_cal / 1024 / cf[0], w_cal / 1024 / cw[0], cf[0], cw[0]
 
 
@@ -253,7 +261,7 @@ def summarize_traffic(directory: str, workload: str, calibration: str = None) ->
                *[f"#   {cmds[n]}" for n in ("pmc_fetch", "pmc_write", "cal_fetch", "cal_write")],
                "# Each counter is the median over the kernel's launches, in KiB per dispatch, scaled by the same",
                "# counter's reading for the calibration: a 4 GiB contiguous copy (4 GiB read, 4 GiB written) by",
-               "# copy_generic_kernel<true>.  --no-fill: the KV buffers are not initialised (the copies move the",
+               f"# {_copy_symbol('unit', CALIBRATION_SEG)}.  --no-fill: the KV buffers are not initialised (the copies move the",
                "# same bytes); the input fill is never run under --pmc.",
                f"kernel={kern}", f"symbol={sym}", f"workload={workload}", f"source_digest={_src_digest()}",
                f"timed_variant={variant}" + ("" if kern == "kv_copy_store" or kern.endswith(variant) else
@@ -567,16 +575,22 @@ def _store_shape_copy(torch, reps: int = 5) -> dict:
             "what": "4 GiB contiguous copy by the store gather's kernel (1024-lane workgroups, non-temporal)"}
 
 
+# The calibration copy: 2,048 slots of two 1 MiB segments (512 tokens), above the window copies' largest, so that
+# it runs the generic copy and no kernel that the counters are read for.
+CALIBRATION_SLOTS, CALIBRATION_SEG = 2048, 512 * 8 * 128 * 2
+
+
 def _calibration_copy(torch, reps: int = 5) -> dict:
     """A plain contiguous copy of known size, run by the library's own copy
-    kernel: one layer, block size == chunk size, block_first paged layout and
-    an identity block table make the retrieve scatter a 4 GiB memcpy (the
-    paged block [2][B][H][D] and the staged chunk [1][2][C][H][D] are the same
-    bytes).  Used to scale hardware byte counters.  Launches no other kernel."""
+    kernel for the largest segments: one layer, block size == chunk size,
+    block_first paged layout and an identity block table make the retrieve
+    scatter a 4 GiB memcpy (the paged block [2][B][H][D] and the staged chunk
+    [1][2][C][H][D] are the same bytes).  Used to scale hardware byte counters.
+    Launches no other kernel."""
     import numpy as np
     import paper_2609_35065_amd as kv
-    n, seg = 4096, 256 * 8 * 128 * 2          # 4096 slots of 1 MiB; segment = one plane of a chunk
-    lo = kv.make_layout(1, 8, 128, 2, 256, 256, n, n, seg, 2 * seg)
+    n, seg = CALIBRATION_SLOTS, CALIBRATION_SEG
+    lo = kv.make_layout(1, 8, 128, 2, seg // 2048, seg // 2048, n, n, seg, 2 * seg)
     stg = torch.empty(n * 2 * seg, dtype=torch.uint8, device="cuda")
     pool = torch.empty(n * 2 * seg, dtype=torch.uint8, device="cuda")
     bt = torch.from_numpy(np.arange(n, dtype=np.int32).reshape(n, 1)).cuda()
@@ -591,7 +605,7 @@ def _calibration_copy(torch, reps: int = 5) -> dict:
     e.record()
     torch.cuda.synchronize()
     ms = s.elapsed_time(e) / reps
-    return {"calibration": "contiguous copy by copy_generic_kernel<true> (the retrieve's generic path, cached "
+    return {"calibration": f"contiguous copy by {_copy_symbol('unit', seg)} (the retrieve's generic path, cached "
                            "loads)", "bytes_read_per_dispatch": n * 2 * seg,
             "bytes_written_per_dispatch": n * 2 * seg, "dispatches": reps + 1, "ms": round(ms, 4),
             "GB/s_rw": round(2 * n * 2 * seg / (ms * 1e-3) / 1e9, 1)}
@@ -663,9 +677,9 @@ def _controller_bench() -> dict:
 
 def _host_link_gbs(torch, nbytes: int = 1 << 30, reps: int = 3) -> dict:
     """Host-link context for workloads staged in host memory: a DMA copy of a
-    pinned buffer into HBM, and the library's copy kernel reading the same
-    buffer through its device mapping (the calibration layout of
-    _calibration_copy: contiguous, identity table)."""
+    pinned buffer into HBM, and the retrieve reading the same buffer through
+    its device mapping (contiguous: one layer, 512 KiB segments, identity
+    table)."""
     import numpy as np
     import paper_2609_35065_amd as kv
     host = torch.empty(nbytes, dtype=torch.uint8, pin_memory=True)

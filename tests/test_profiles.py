@@ -46,6 +46,18 @@ def test_symbols_follow_the_segment_size():
     assert bench._symbol("stream", t) == "group_copy_kernel<256, 1, true>"
 
 
+def test_calibration_runs_the_kernel_it_is_read_by():
+    # the counters' calibration must run a kernel of its own: the generic copy, above the window copies' segments
+    text = open(os.path.join(CSRC, "window.h")).read()
+    limits = [eval(re.search(rf"{name} = ([0-9 <]+);", text).group(1)) for name in ("kMinWindowSeg", "kMaxWindowSeg")]
+    assert tuple(limits) == bench.WINDOW_SEGMENTS
+    assert bench.CALIBRATION_SEG > limits[1]
+    assert bench._copy_symbol("unit", bench.CALIBRATION_SEG) == "copy_generic_kernel<true>"
+    for seg in limits:
+        assert bench._copy_symbol("unit", seg).startswith("retrieve_unit_kernel")
+    assert bench.CALIBRATION_SLOTS * 2 * bench.CALIBRATION_SEG == 4 << 30
+
+
 def _write_csv(path, rows):
     os.makedirs(os.path.dirname(path), exist_ok=True)
     with open(path, "w", newline="") as f:
@@ -73,7 +85,7 @@ def test_traffic_summary_scales_by_the_calibration(tmp_path, monkeypatch):
     d = tmp_path / "prof"
     store = "tkv::(anonymous namespace)::group_copy_kernel<1024, 2, false>(tkv::CopyParams)"
     quad = "tkv::(anonymous namespace)::retrieve_quad_kernel<8>(tkv::CopyParams)"
-    cal = "tkv::(anonymous namespace)::copy_generic_kernel<true>(tkv::CopyParams)"
+    cal = f"tkv::(anonymous namespace)::{bench._copy_symbol('unit', bench.CALIBRATION_SEG)}(tkv::CopyParams)"
     row = lambda k, c, v: {"Kernel_Name": k, "Counter_Name": c, "Counter_Value": str(v)}
     _write_csv(str(d / "pmc_fetch" / "c_counter_collection.csv"), [row(store, "FETCH_SIZE", 100), row(quad, "FETCH_SIZE", 10)])
     _write_csv(str(d / "pmc_write" / "c_counter_collection.csv"), [row(store, "WRITE_SIZE", 200), row(quad, "WRITE_SIZE", 50)])
@@ -100,7 +112,7 @@ def test_ceiling_summary_takes_the_ceiling_launches(tmp_path, monkeypatch):
     d = tmp_path / "prof"
     quad = "tkv::(anonymous namespace)::retrieve_quad_kernel<8>(tkv::CopyParams)"
     red = "void at::native::reduce_kernel<512, 1>(at::native::ReduceOp<long>)"
-    cal = "tkv::(anonymous namespace)::copy_generic_kernel<true>(tkv::CopyParams)"
+    cal = f"tkv::(anonymous namespace)::{bench._copy_symbol('unit', bench.CALIBRATION_SEG)}(tkv::CopyParams)"
     n = bench.CEILING_LAUNCHES
 
     def rows(ctr, real, ceil, reader):
