@@ -55,12 +55,18 @@ def _src_digest() -> str:
     return h.hexdigest()[:16]
 
 
+def _same_copy(variant):
+    """The retrieve variant under whose name the traffic of a variant's copy is kept: PAIR runs UNIT's."""
+    return "unit" if variant == "pair" else variant
+
+
 def _load_traffic(kernel: str, workload: str, variant: str = None):
     """HBM bytes per launch measured by rocprofv3 counters, if a summary for
     this kernel (retrieve: and variant) and workload exists and was taken from
     the current source."""
     if kernel == "kv_copy_retrieve" and variant is None:
         return None
+    variant = _same_copy(variant)
     tag = f"{kernel}_{variant}" if kernel == "kv_copy_retrieve" else kernel
     path = os.path.join(PROFILES, f"traffic_{tag}_{workload}.txt")
     if not os.path.exists(path):
@@ -246,9 +252,9 @@ def summarize_traffic(directory: str, workload: str, calibration: str = None) ->
     w = W.make(workload)
     out = []
     kinds = [("kv_copy_store", _symbol("store", w))]
-    for v in ("unit", "pair", "quad", "stream"):
-        # the timed variant, and the candidate the retrieve tuning also launched in the same run
-        if _symbol(v, w) not in [k for k, _ in kinds]:
+    for v in ("unit", "quad", "stream"):
+        # the timed variant's copy, and the candidate the retrieve tuning also launched in the same run
+        if _symbol(v, w) not in [k for _, k in kinds]:
             kinds.append((f"kv_copy_retrieve_{v}", _symbol(v, w)))
     for kern, sym in kinds:
         fk = [v for (k, c), v in fe.items() if k == sym and c == "FETCH_SIZE"]
@@ -264,7 +270,7 @@ def summarize_traffic(directory: str, workload: str, calibration: str = None) ->
                f"# {_copy_symbol('unit', CALIBRATION_SEG)}.  --no-fill: the KV buffers are not initialised (the copies move the",
                "# same bytes); the input fill is never run under --pmc.",
                f"kernel={kern}", f"symbol={sym}", f"workload={workload}", f"source_digest={_src_digest()}",
-               f"timed_variant={variant}" + ("" if kern == "kv_copy_store" or kern.endswith(variant) else
+               f"timed_variant={variant}" + ("" if kern == "kv_copy_store" or kern.endswith(_same_copy(variant)) else
                                               " (this variant ran in the retrieve tuning before the timed steps)"),
                f"fetch_kib_per_dispatch={fk:.1f}", f"write_kib_per_dispatch={wk:.1f}",
                f"calibration_fetch_kib={cf:.1f}", f"calibration_write_kib={cw:.1f}",

@@ -107,6 +107,24 @@ def test_traffic_summary_scales_by_the_calibration(tmp_path, monkeypatch):
     assert bench._load_traffic("kv_copy_retrieve", "l32-64x4096", "pair") is None
 
 
+def test_traffic_of_a_planned_pair_is_kept_and_found(tmp_path, monkeypatch):
+    # the planner's PAIR runs UNIT's copy: its traffic is written and read under one name
+    monkeypatch.setattr(bench, "PROFILES", str(tmp_path))
+    d = tmp_path / "prof"
+    ns = "tkv::(anonymous namespace)::"
+    row = lambda k, c, v: {"Kernel_Name": f"{ns}{k}(tkv::CopyParams)", "Counter_Name": c, "Counter_Value": str(v)}
+    unit, cal = "retrieve_unit_kernel<1>", bench._copy_symbol("unit", bench.CALIBRATION_SEG)
+    for kind, c in (("fetch", "FETCH_SIZE"), ("write", "WRITE_SIZE")):
+        _write_csv(str(d / f"pmc_{kind}" / "c_counter_collection.csv"), [row(unit, c, 70)])
+        _write_csv(str(d / f"cal_{kind}" / "c_counter_collection.csv"), [row(cal, c, 4 << 20)])
+    (d / "pmc_fetch.log").write_text('{"config": {"retrieve_variant": "pair"}}\n')
+    paths = bench.summarize_traffic(str(d), "l32-64x4096")
+    assert [os.path.basename(p) for p in paths] == ["traffic_kv_copy_retrieve_unit_l32-64x4096.txt"]
+    assert "timed_variant=pair\n" in open(paths[0]).read()
+    for variant in ("pair", "unit"):
+        assert bench._load_traffic("kv_copy_retrieve", "l32-64x4096", variant) == 140 * 1024
+
+
 def test_ceiling_summary_takes_the_ceiling_launches(tmp_path, monkeypatch):
     monkeypatch.setattr(bench, "PROFILES", str(tmp_path))
     d = tmp_path / "prof"
