@@ -474,7 +474,8 @@ def _layer_array(layers: Sequence) -> array:
     if all(type(t) is tensor for t in layers) and all(map(tensor.is_cuda.__get__, layers)) \
             and all(map(tensor.is_contiguous, layers)):
         return array("Q", map(tensor.data_ptr, layers))
-    return array("Q", [_dptr(t, None, f"layer {i}") for i, t in enumerate(layers)])
+    # (an address may come as a signed number, as in ctypes' own arrays of pointers)
+    return array("Q", [_dptr(t, None, f"layer {i}") & 0xFFFFFFFFFFFFFFFF for i, t in enumerate(layers)])
 
 
 def kv_retrieve_scatter(layout: KvLayout, d_staging, layers: Sequence, d_block_tables, bt_stride: int,

@@ -325,3 +325,9 @@ def test_chunk_keys_match_oracle(seed):
             bad = chunk_off.copy()
             bad[-1] += 1
             kv.kv_chunk_keys(bh, blk_off, bpc, bad)
+
+
+def test_layer_addresses_may_be_signed():
+    # what a C array of pointers takes: 64-bit addresses, also as signed numbers
+    lp = kv._layer_array([4096, -4096, 2 ** 64 - 16, 2 ** 64 + 32])
+    assert list(lp) == [4096, 2 ** 64 - 4096, 2 ** 64 - 16, 32]
