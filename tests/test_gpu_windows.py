@@ -12,8 +12,8 @@ pytestmark = pytest.mark.gpu
 
 MIB = 1 << 20
 # (block, heads, dim, elem): 496 B and 1 MiB segments take the generic copy; 512 B is the smallest window segment;
-# 1,040 B leaves rows that cross segments at every offset; the rest are 1.25, 4, 20, 32, 64 and 512 KiB
-SHAPES = {"496": (1, 1, 248, 2), "512": (16, 1, 32, 1), "1040": (13, 1, 40, 2), "1280": (16, 1, 80, 1),
+# 528 and 1,040 B leave rows that cross segments at every offset; the rest are 1.25, 4, 20, 32, 64 and 512 KiB
+SHAPES = {"496": (1, 1, 248, 2), "512": (16, 1, 32, 1), "528": (33, 1, 16, 1), "1040": (13, 1, 40, 2), "1280": (16, 1, 80, 1),
           "4k": (16, 1, 128, 2), "20k": (16, 8, 80, 2), "32k": (16, 8, 128, 2), "64k": (16, 8, 128, 4),
           "512k": (128, 8, 128, 4), "1m": (256, 8, 128, 4)}
 
@@ -122,11 +122,27 @@ def test_host_memory(mib, shape, op):
     _check(shape, mib * MIB, op, "kv_first", 0, 17, host=True)
 
 
+@pytest.mark.parametrize("shape", ["64k", "512k"])
+@pytest.mark.parametrize("mib", [100, 700])
+def test_planes_above_a_group(mib, shape):
+    # planes of 1 MiB: groups of 256 windows, several jobs to a slot
+    _check(shape, mib * MIB, "unit", "block_first", 0, 19)
+
+
+@pytest.mark.parametrize("op", ["store", "stream"])
+@pytest.mark.parametrize("shape", ["512", "528"])
+@pytest.mark.parametrize("mib", [60, 1100])
+def test_many_segments_a_window(mib, shape, op):
+    # windows of 16 KiB over up to 33 segments: every lane of the address table in use
+    _check(shape, mib * MIB, op, "kv_first", 0, 23)
+
+
+@pytest.mark.parametrize("shape", ["4k", "32k"])
 @pytest.mark.parametrize("host", [False, True])
-def test_shared_retrieve_captured(host):
+def test_shared_retrieve_captured(host, shape):
     # The shared retrieve asks where the staged chunks lie before it launches: from device and from host memory,
     # eager and captured (replayed three times, with eager work and a synchronisation between).
-    lo, pool, staging, bt, jobs, ok, dims = _setup(SHAPES["32k"], 20 * MIB, 0.3, "kv_first", 0, 5)
+    lo, pool, staging, bt, jobs, ok, dims = _setup(SHAPES[shape], 20 * MIB, 0.3, "kv_first", 0, 5)
     want, _ = _expected(pool, staging, bt, jobs, ok, dims, False)
     if host:
         pinned = torch.empty(staging.numel(), dtype=torch.int64, pin_memory=True)
