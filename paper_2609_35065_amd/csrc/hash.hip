@@ -22,9 +22,11 @@
 // 7.4 us an entry at a time, 4.0 by four, 3.7 by eight).  Where full waves are
 // many, the address rate bounds it instead, and most walks end at their first
 // entry: those lanes read it alone first (4,096 requests of 64 present chunks
-// 10.5 us, 12.7 without, 10.5 an entry at a time; of 256, 33 us, 42 and 40).  The
-// rule asks for 1,024 requests, and 64 chunks of this one: 100,000 requests of 4
-// chunks take 46 us with it and 41 without, 64 requests of 4,096 89 and 68.
+// 8.6 us, 11.3 without, 10.8 an entry at a time; of 256, 33 us, 42 and 40).  The
+// rule asks for 2,048 requests, and 64 chunks of this one: 100,000 requests of 4
+// chunks take 46 us with it and 41 without, 64 requests of 4,096 89 and 68; at
+// 1,024 requests of 64 both take 3.7.  Smaller batches run a kernel without the
+// question: it would cost them 0.3 of 2.8 us.
 
 #include "internal.h"
 
@@ -35,7 +37,7 @@ constexpr uint64_t kGamma = 0x9E3779B97F4A7C15ull;
 constexpr int kWave = 64;
 constexpr int kHashThreads = 256;
 constexpr int kProbes = 8;
-constexpr uint32_t kFirstRequests = 1024;
+constexpr int32_t kFirstRequests = 2048;
 constexpr int64_t kFirstChunks = 64;
 static_assert(64 % kProbes == 0, "tables have at least 64 entries, a power of two");
 
@@ -199,6 +201,7 @@ __global__ __launch_bounds__(kHashThreads) void hash_kernel(const int32_t *__res
     }
 }
 
+template <bool kLarge>
 __global__ __launch_bounds__(64) void lookup_kernel(const IndexEntry *__restrict__ table, int log2cap,
                                                     const uint64_t *__restrict__ bh,
                                                     const int64_t *__restrict__ blk_off, int32_t bpc,
@@ -216,7 +219,7 @@ __global__ __launch_bounds__(64) void lookup_kernel(const IndexEntry *__restrict
     if (cspan < nc) nc = cspan > 0 ? cspan : 0;
     const uint64_t mask = (uint64_t(1) << log2cap) - 1;
 
-    const bool first_alone = gridDim.x >= kFirstRequests && nc >= kFirstChunks;
+    const bool first_alone = kLarge && nc >= kFirstChunks;
     int32_t hits = 0;
     bool alive = true;
     for (int64_t base = 0; base < nc; base += 64) {
@@ -274,8 +277,8 @@ hipError_t launch_lookup(const IndexEntry *table, int log2cap, const uint64_t *b
                          int32_t *chunk_slot, int32_t *hit_chunks, hipStream_t stream) {
     if (num_reqs <= 0) return hipSuccess;
     (void)hipGetLastError();
-    hipLaunchKernelGGL(lookup_kernel, dim3(num_reqs), dim3(64), 0, stream, table, log2cap, block_hash, blk_off,
-                       bpc, chunk_off, chunk_slot, hit_chunks);
+    hipLaunchKernelGGL(num_reqs >= kFirstRequests ? lookup_kernel<true> : lookup_kernel<false>, dim3(num_reqs), dim3(64),
+                       0, stream, table, log2cap, block_hash, blk_off, bpc, chunk_off, chunk_slot, hit_chunks);
     return hipGetLastError();
 }
 

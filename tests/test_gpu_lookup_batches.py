@@ -1,5 +1,5 @@
 """Lookups on both sides of the sizes at which a lane reads the first entry of
-its walk alone (1,024 requests, 64 chunks of a request), in a table with erased
+its walk alone (2,048 requests, 64 chunks of a request), in a table with erased
 keys and long walks, against the oracle (whole numbers, so exactly)."""
 import numpy as np
 import pytest
@@ -11,7 +11,7 @@ import paper_2609_35065_amd as kv
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("requests", [1023, 1024, 1500])
+@pytest.mark.parametrize("requests", [2047, 2048, 3000])
 def test_batches(requests):
     rng = np.random.default_rng(requests)
     live = 4000                                             # of 8,192 positions
