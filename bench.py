@@ -107,14 +107,19 @@ def _copy_symbol(kind: str, seg: int) -> str:
     return f"group_copy_kernel<{256 if retrieve and seg < 16384 else 1024}, {row}, {'true' if retrieve else 'false'}>"
 
 
-def _symbol(kind: str, w) -> str:
-    return _copy_symbol(kind, w.shape.seg_bytes)
+def _symbol(kind: str, w, in_place: bool = False) -> str:
+    """_copy_symbol for a workload; in_place: its staged chunks are read from host memory, where shared retrieves
+    run the small copy's shape at any size."""
+    seg = w.shape.seg_bytes
+    sym = _copy_symbol(kind, seg)
+    if in_place and sym.startswith("retrieve_unit_kernel"):
+        return f"small_copy_kernel<256, 2, 2, {1 if seg % 1024 == 0 else 0}>"
+    return sym
 
 
 def _label(symbol: str) -> str:
     """What a library kernel does, from its symbol."""
     for key, text in (("retrieve_unit_kernel", "retrieve scatter, shared chunks (KV_RETRIEVE_UNIT, KV_RETRIEVE_PAIR)"),
-                      ("small_copy_kernel", "retrieve scatter or store gather, small launch"),
                       ("retrieve_quad_kernel", "retrieve scatter, four-job window (KV_RETRIEVE_QUAD)"),
                       ("copy_generic_kernel<true>", "retrieve scatter, generic path"),
                       ("copy_generic_kernel<false>", "store gather, generic path"),
@@ -125,6 +130,10 @@ def _label(symbol: str) -> str:
                                                "(kv_probe_mixed_traffic)")):
         if key in symbol:
             return text
+    if "small_copy_kernel" in symbol:
+        mode = symbol[symbol.index("<") + 1:].split(",")[2].strip()
+        return {"0": "store gather, small launch", "1": "retrieve scatter, streaming, small launch",
+                "2": "retrieve scatter, small launch or chunks in host memory"}[mode]
     if "group_copy_kernel" in symbol:
         return ("retrieve scatter, streaming (KV_RETRIEVE_STREAM)" if "true>" in symbol
                 else "store gather (kv_store_gather)")
@@ -267,8 +276,9 @@ def summarize_traffic(directory: str, workload: str, calibration: str = None) ->
                *[f"#   {cmds[n]}" for n in ("pmc_fetch", "pmc_write", "cal_fetch", "cal_write")],
                "# Each counter is the median over the kernel's launches, in KiB per dispatch, scaled by the same",
                "# counter's reading for the calibration: a 4 GiB contiguous copy (4 GiB read, 4 GiB written) by",
-               f"# {_copy_symbol('unit', CALIBRATION_SEG)}.  --no-fill: the KV buffers are not initialised (the copies move the",
-               "# same bytes); the input fill is never run under --pmc.",
+               f"# {_copy_symbol('unit', CALIBRATION_SEG)}.",
+               "# --no-fill: the KV buffers are not initialised (the copies move the same bytes); the input fill is",
+               "# never run under --pmc.",
                f"kernel={kern}", f"symbol={sym}", f"workload={workload}", f"source_digest={_src_digest()}",
                f"timed_variant={variant}" + ("" if kern == "kv_copy_store" or kern.endswith(_same_copy(variant)) else
                                               " (this variant ran in the retrieve tuning before the timed steps)"),
@@ -938,7 +948,8 @@ def main() -> int:
     per_kernel = {
         "store_gather": {"symbol": _symbol("store", w), "achieved": round(s_gbs, 1),
                          "frac": round(s_gbs / HBM_PEAK_GBS, 4), "traffic": _load_traffic("kv_copy_store", args.workload)},
-        "retrieve_scatter": {"symbol": _symbol(variant, w) if variant else None, "achieved": round(r_hbm, 1),
+        "retrieve_scatter": {"symbol": (_symbol(variant, w, w.staging_in_host and not path.staged_mode) if variant
+                                        else None), "achieved": round(r_hbm, 1),
                              "frac": round(r_hbm / HBM_PEAK_GBS, 4),
                              "traffic": _load_traffic("kv_copy_retrieve", args.workload, variant)},
     }

@@ -90,9 +90,10 @@ __device__ __forceinline__ bool blk_ok(const CopyParams &p, int32_t blk) {
 // the index is below segv + 1024 and the bracket below segv, so it holds for
 // segv <= 32768 (kMaxWindowSeg).
 // --------------------------------------------------------------------------
-enum WindowMode { kWinStore, kWinStream, kWinShared };
+// Modes (plain numbers, so that a profiler's kernel names show them).
+constexpr int kWinStore = 0, kWinStream = 1, kWinShared = 2;
 
-template <int T, int V, WindowMode kMode, int kRow>
+template <int T, int V, int kMode, int kRow>
 __device__ __forceinline__ void copy_window(const CopyParams &p, const WindowParams &w) {
     static_assert(V * 64 <= 1024, "the bound of magic and the lane table allow 1024 vectors a window");
     constexpr uint32_t W = T / 64;
@@ -186,7 +187,7 @@ __global__ __launch_bounds__(256) void retrieve_unit_kernel(CopyParams p, Window
 
 // The same for launches that the memory-side caches or one set of resident
 // waves hold.
-template <int T, int V, WindowMode kMode, int kRow>
+template <int T, int V, int kMode, int kRow>
 __global__ __launch_bounds__(T) void small_copy_kernel(CopyParams p, WindowParams w) {
     copy_window<T, V, kMode, kRow>(p, w);
 }
@@ -315,7 +316,7 @@ void launch_group(const CopyParams &p, const WindowParams &w, hipStream_t s) {
         TKV_LAUNCH_WINDOW(T, (group_copy_kernel<T, 0, kRetrieve>));
 }
 
-template <int T, int V, WindowMode kMode>
+template <int T, int V, int kMode>
 void launch_small(const CopyParams &p, const WindowParams &w, hipStream_t s) {
     if (p.seg_bytes % 1024 == 0)
         TKV_LAUNCH_WINDOW(T, (small_copy_kernel<T, V, kMode, 1>));
@@ -337,7 +338,7 @@ double payload_of(const CopyParams &p) { return (double)p.slot_bytes * p.num_job
 
 template <bool kRetrieve>
 bool launch_stream_shape(const CopyParams &p, const CopyShape &c, hipStream_t s) {
-    constexpr WindowMode kMode = kRetrieve ? kWinStream : kWinStore;
+    constexpr int kMode = kRetrieve ? kWinStream : kWinStore;
     WindowParams w;
     if (!window_params(p.seg_bytes, p.slot_bytes, p.num_jobs, c.vectors, c.group, w)) return false;
     if (kRetrieve && c.cached && c.vectors == 2) launch_small<256, 2, kWinShared>(p, w, s);
