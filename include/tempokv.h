@@ -241,8 +241,9 @@ int kv_retrieve_scatter(const kv_layout *layout, const void *d_staging, void *co
 /* Variants of the retrieve.  All give the bytes of kv_retrieve_scatter for
  * any job list; they differ in speed by the way jobs share staged chunks. */
 typedef enum kv_retrieve_kind {
-    KV_RETRIEVE_UNIT = 0,   /* groups of 512 KiB or more, job after job: jobs that share a chunk read a group
-                               through the L2 (kv_retrieve_scatter) */
+    KV_RETRIEVE_UNIT = 0,   /* groups of 32 KiB to 1 MiB by the launch's size, job after job: jobs that share a
+                               chunk and follow one another (kv_group_jobs_by_slot) read a group through the
+                               L2 (kv_retrieve_scatter) */
     KV_RETRIEVE_PAIR = 1,   /* runs as UNIT, which is the faster also where pairs of jobs name one chunk */
     KV_RETRIEVE_STREAM = 2, /* non-temporal loads of the staged chunks: for lists that read each chunk once */
     KV_RETRIEVE_QUAD = 3    /* one 1024-lane workgroup per (layer, plane, 4 consecutive jobs, segment): jobs of
@@ -277,8 +278,9 @@ int kv_store_gather(const kv_layout *layout, void *d_staging, const void *const 
 /* Reorder a job list in host memory so that jobs naming the same staging
  * slot are adjacent (stable: by slot, then original order).  The copies'
  * results do not depend on job order (destinations are disjoint within a
- * call); the retrieve kernel reads a staged chunk once per unit when the
- * jobs sharing it run back to back.  Errors: KV_EINVAL. */
+ * call); when the jobs sharing a chunk run back to back, all but the first
+ * read it from the L2.  Large launches on lists in another order can take up
+ * to 1.8 times as long (4 KiB segments, 6 GiB).  Errors: KV_EINVAL. */
 int kv_group_jobs_by_slot(kv_job *h_jobs, int32_t num_jobs);
 
 /* ----------------------------------------------------------------------- */

@@ -3,36 +3,38 @@
 //
 // Vocabulary.  A segment is the B tokens of one layer's K or V plane that
 // form one paged block: B*H*D*e contiguous bytes on both sides (32 KiB for
-// block 16 x 8 heads x 128 dims x bf16).  A unit is the C/B segments of one
-// (job, layer, plane): contiguous in the staged chunk, one paged block each.
-// A row is one 16-byte vector per lane of a workgroup (T*16 bytes, one wave
-// instruction per 64 lanes covering 1 KiB of contiguous memory).
+// block 16 x 8 heads x 128 dims x bf16).  A plane is the C/B segments of one
+// (job, layer, K or V): contiguous in the staged chunk, one paged block each.
+// A row is 1 KiB of contiguous memory, one 16-byte vector per lane of a wave.
 //
-// A window is V consecutive 1 KiB rows of a staged slot (one 16-byte vector
-// per lane of one wave and row).  The staged side of a window is contiguous;
-// on the paged side it covers parts of one or more segments, of one or two
-// planes, whatever the segment size.
+// A window is V consecutive rows of a staged slot.  The staged side of a window
+// is contiguous; on the paged side it covers parts of one or more segments, of
+// one or two planes, whatever the segment size.
 //
 // Both directions run copy_window: one wave per window, T/64 consecutive
 // windows of the launch's order (window.h) per workgroup, all loads of a window
-// before its stores.  What bounds
-// a copy is how the memory system takes its order of reads and writes, so the
-// three shapes differ in how much a wave moves and which windows are in flight
-// together:
+// before its stores.  What bounds a copy is how the memory system takes its
+// order of reads and writes, so the shapes differ in how much a wave moves and
+// which windows are in flight together:
 //
 //   Store and streaming retrieve (no staged byte read twice): job-major order,
 //   each XCD taking one contiguous range of it, non-temporal on both sides.
 //   Large launches move 16 KiB per wave in 1024-lane workgroups; small ones
-//   2 KiB per wave, so that every CU has work and the first store is issued
-//   early (stream_shape in window.h has the sizes and times).
+//   mostly 2 KiB per wave, so that every CU has work and the first store is
+//   issued early (stream_shape in window.h has the sizes and times, and where
+//   a streaming retrieve reads through the caches).
 //
-//   Retrieve where jobs share staged chunks: 4 KiB per wave, 256-lane
-//   workgroups, in groups of windows (512 KiB or more); a group of one job is
-//   followed by the same group of the next job, and each XCD takes one
-//   contiguous range of that order.  Jobs that share a chunk (adjacent once
-//   the job list is grouped by slot) read the group through one XCD's L2 while
-//   it is there, and a paged block is written by workgroups that run together.
-//   Loads are cached, paged writes non-temporal.
+//   Retrieve where jobs share staged chunks: 4 KiB per wave (2 KiB in small
+//   launches), 256-lane workgroups, in groups of windows (shared_shape in
+//   window.h: 32 KiB to 1 MiB); a group of one job is followed by the same group
+//   of the next job, and each XCD takes one contiguous range of that order.
+//   Jobs that share a chunk (adjacent once the job list is grouped by slot) read
+//   the group through one XCD's L2 while it is there, and a paged block is
+//   written by workgroups that run together.  Loads are cached, paged writes
+//   non-temporal.
+//
+//   Staged chunks in host memory: shapes of their own (window.h), since what
+//   bounds those copies is the link.
 //
 // A further retrieve, the four-job-window retrieve (one segment of four
 // consecutive jobs per 1024-lane workgroup), runs where a caller names it: 3.69
@@ -82,8 +84,8 @@ __device__ __forceinline__ bool blk_ok(const CopyParams &p, int32_t blk) {
 // whole KiB); 0, lane by lane through ds_bpermute.  So any segment of at least
 // kMinWindowSeg bytes fills its lanes, where one workgroup per segment leaves
 // three of four waves of a 1 KiB segment without work: 512 jobs of 1 KiB
-// segments store in 0.19 ms (0.75 ms before), retrieve with shared chunks
-// (1,422 jobs) in 0.37 ms (2.07 ms before).
+// segments store in 0.19 ms (one workgroup per segment: 0.75 ms), retrieve with
+// shared chunks (1,422 jobs) in 0.37 ms (2.07 ms).
 //
 // The division of a row's vector index by the segment size is a multiply by
 // magic = ceil(2^32 / segv), exact while index * (magic * segv - 2^32) < 2^32:
@@ -185,8 +187,7 @@ __global__ __launch_bounds__(256) void retrieve_unit_kernel(CopyParams p, Window
     copy_window<256, 4, kWinShared, kRow>(p, w);
 }
 
-// The same for launches that the memory-side caches or one set of resident
-// waves hold.
+// The other shapes: launches of up to 1 GiB, and shared chunks in host memory.
 template <int T, int V, int kMode, int kRow>
 __global__ __launch_bounds__(T) void small_copy_kernel(CopyParams p, WindowParams w) {
     copy_window<T, V, kMode, kRow>(p, w);
