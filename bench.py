@@ -107,14 +107,8 @@ def _copy_symbol(kind: str, seg: int) -> str:
     return f"group_copy_kernel<{256 if retrieve and seg < 16384 else 1024}, {row}, {'true' if retrieve else 'false'}>"
 
 
-def _symbol(kind: str, w, in_place: bool = False) -> str:
-    """_copy_symbol for a workload; in_place: its staged chunks are read from host memory, where shared retrieves
-    run the small copy's shape at any size."""
-    seg = w.shape.seg_bytes
-    sym = _copy_symbol(kind, seg)
-    if in_place and sym.startswith("retrieve_unit_kernel"):
-        return f"small_copy_kernel<256, 2, 2, {1 if seg % 1024 == 0 else 0}>"
-    return sym
+def _symbol(kind: str, w) -> str:
+    return _copy_symbol(kind, w.shape.seg_bytes)
 
 
 def _label(symbol: str) -> str:
@@ -133,7 +127,7 @@ def _label(symbol: str) -> str:
     if "small_copy_kernel" in symbol:
         mode = symbol[symbol.index("<") + 1:].split(",")[2].strip()
         return {"0": "store gather, small launch", "1": "retrieve scatter, streaming, small launch",
-                "2": "retrieve scatter, small launch or chunks in host memory"}[mode]
+                "2": "retrieve scatter, small launch"}[mode]
     if "group_copy_kernel" in symbol:
         return ("retrieve scatter, streaming (KV_RETRIEVE_STREAM)" if "true>" in symbol
                 else "store gather (kv_store_gather)")
@@ -948,8 +942,7 @@ def main() -> int:
     per_kernel = {
         "store_gather": {"symbol": _symbol("store", w), "achieved": round(s_gbs, 1),
                          "frac": round(s_gbs / HBM_PEAK_GBS, 4), "traffic": _load_traffic("kv_copy_store", args.workload)},
-        "retrieve_scatter": {"symbol": (_symbol(variant, w, w.staging_in_host and not path.staged_mode) if variant
-                                        else None), "achieved": round(r_hbm, 1),
+        "retrieve_scatter": {"symbol": _symbol(variant, w) if variant else None, "achieved": round(r_hbm, 1),
                              "frac": round(r_hbm / HBM_PEAK_GBS, 4),
                              "traffic": _load_traffic("kv_copy_retrieve", args.workload, variant)},
     }

@@ -187,7 +187,7 @@ __global__ __launch_bounds__(256) void retrieve_unit_kernel(CopyParams p, Window
     copy_window<256, 4, kWinShared, kRow>(p, w);
 }
 
-// The other shapes: launches of up to 1 GiB, and shared chunks in host memory.
+// The other shapes: launches of up to 1 GiB.
 template <int T, int V, int kMode, int kRow>
 __global__ __launch_bounds__(T) void small_copy_kernel(CopyParams p, WindowParams w) {
     copy_window<T, V, kMode, kRow>(p, w);

@@ -180,20 +180,25 @@ constexpr CopyShape stream_shape(bool retrieve, double payload, int64_t seg_byte
 //   600 MiB of 16 KiB, 64 KiB    237   168   119   118
 //                      32 KiB    236   193   110   115
 //
-// Staged chunks in host memory are read through the link, where what counts is
-// that the jobs sharing a chunk read the same bytes at the same time: groups of
-// 8 KiB, 2 KiB a wave (3,072 jobs on 48 chunks of 16 MiB: 14.1 ms, 16.6 in
-// groups of 64 KiB and 17.9 of 256 KiB; 400 MiB and less: 0-10 % faster than
-// 4 KiB a wave in groups of 16 KiB).  The exception above needs no such rule:
-// groups of 32 KiB measured as fast there.  A single job shares nothing and
-// takes the streaming shape (8 MiB: 158 us; 191 in groups).
+// Staged chunks in host memory are read through the link: the jobs sharing a
+// chunk should read the same bytes at the same time, yet write enough of a
+// block together.  Groups of 32 KiB, 4 KiB a wave, do both (ms by KiB a group;
+// 2,016 jobs of 32 MiB on 12 chunks, 2,568 on 24, 3,072 on 48; 32 KiB segments):
+//                2 KiB a wave: 8    32   128    4 KiB a wave: 16    32    64   512
+//   on 12 chunks            13.9  12.3  12.7                12.5  12.4  12.4  13.5
+//   on 24                   17.3  14.3  17.4                14.2  14.2  14.6  18.5
+//   on 48                   28.3  28.2  32.6                28.2  28.1  33.3  33.1
+// Launches of up to 512 MiB run 2 KiB a wave in groups of 32 KiB, as the small
+// launches of small segments do (24 MiB, three jobs: 158 against 163 us).  A
+// single job shares nothing and takes the streaming shape (8 MiB: 158 us; 191
+// in groups).
 constexpr bool shared_small(double payload, int64_t seg_bytes) {
     return payload <= 512 * kMiB && seg_bytes < 32768;
 }
 
 constexpr CopyShape shared_shape(double payload, int64_t seg_bytes, int64_t plane_bytes, bool host) {
     if (shared_small(payload, seg_bytes)) return {256, 2, 16};
-    if (host) return {256, 2, 4};
+    if (host) return payload <= 512 * kMiB ? CopyShape{256, 2, 16} : CopyShape{256, 4, 8};
     if (seg_bytes < 32768) {
         if (payload <= 1024 * kMiB) return {256, 4, 16};
         if (plane_bytes >= (128 << 10) && plane_bytes <= (512 << 10))
