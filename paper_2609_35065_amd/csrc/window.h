@@ -182,8 +182,9 @@ constexpr CopyShape stream_shape(bool retrieve, double payload, int64_t seg_byte
 //
 // Staged chunks in host memory are read through the link: the jobs sharing a
 // chunk should read the same bytes at the same time, yet write enough of a
-// block together.  Groups of 32 KiB, 4 KiB a wave, do both (ms by KiB a group;
-// 2,016 jobs of 32 MiB on 12 chunks, 2,568 on 24, 3,072 on 48; 32 KiB segments):
+// block together.  Groups of 16 KiB, 4 KiB a wave, do both (ms by KiB a group;
+// 2,016 jobs of 32 MiB on 12 chunks, 2,568 on 24, 3,072 on 48; 32 KiB segments;
+// with ragged sharing, 3,072 on 48 take 29.3 in groups of 16 KiB, 30.2 of 32):
 //                2 KiB a wave: 8    32   128    4 KiB a wave: 16    32    64   512
 //   on 12 chunks            13.9  12.3  12.7                12.5  12.4  12.4  13.5
 //   on 24                   17.3  14.3  17.4                14.2  14.2  14.6  18.5
@@ -198,7 +199,7 @@ constexpr bool shared_small(double payload, int64_t seg_bytes) {
 
 constexpr CopyShape shared_shape(double payload, int64_t seg_bytes, int64_t plane_bytes, bool host) {
     if (shared_small(payload, seg_bytes)) return {256, 2, 16};
-    if (host) return payload <= 512 * kMiB ? CopyShape{256, 2, 16} : CopyShape{256, 4, 8};
+    if (host) return payload <= 512 * kMiB ? CopyShape{256, 2, 16} : CopyShape{256, 4, 4};
     if (seg_bytes < 32768) {
         if (payload <= 1024 * kMiB) return {256, 4, 16};
         if (plane_bytes >= (128 << 10) && plane_bytes <= (512 << 10))

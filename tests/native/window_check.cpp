@@ -68,8 +68,8 @@ int main() {
     CHECK(tkv::window_params(1024, 2048, 0x7fffff00, 2, 16, w) && w.total == 0x7fffff00u);
     CHECK(!tkv::window_params(1024, 2048, 0x7fffff01, 2, 16, w));
     // launch shapes: with the chunks in host memory a retrieve of up to 48 MiB reads 16 KiB a wave, other small
-    // copies move 2 KiB a wave, and jobs that share a chunk take groups of 32 KiB; the question is asked wherever
-    // the answer matters
+    // copies move 2 KiB a wave, and jobs that share a chunk take groups of 32 KiB up to 512 MiB and of 16 KiB
+    // above; the question is asked wherever the answer matters
     for (double mib = 0.5; mib < 4096; mib *= 1.1)
         for (int64_t seg : {1024, 20480, 32768, 65536})
             for (int retrieve = 0; retrieve < 2; ++retrieve) {
@@ -80,7 +80,7 @@ int main() {
                 if (!tkv::stream_asks_host(retrieve, bytes)) CHECK(d.threads == h.threads && d.vectors == h.vectors);
                 const tkv::CopyShape sh = tkv::shared_shape(bytes, seg, 16 * seg, true);
                 const tkv::CopyShape sd = tkv::shared_shape(bytes, seg, 16 * seg, false);
-                CHECK(sh.vectors * sh.group == 32 && sh.vectors == (mib <= 512 ? 2 : 4));
+                CHECK(sh.vectors == (mib <= 512 ? 2 : 4) && sh.group == (mib <= 512 ? 16 : 4));
                 if (tkv::shared_small(bytes, seg)) CHECK(sh.vectors == sd.vectors && sh.group == sd.group);
                 // cached loads: from 24 to 256 MiB of segments that are not 4 KiB x 2^n
                 CHECK(d.cached == (retrieve && (seg == 1024 || seg == 20480) && mib > 24 && mib <= 256));
